@@ -1428,6 +1428,7 @@ static int32_t build_tables(lbmdem_batch* b) {
   b->t.claim_start = (const int*)(m + tb + ib);
   b->t.commit_start = (const int*)(m + tb + 2 * ib);
   b->t.ndom = nd;
+  b->t.max_P = nd ? *std::max_element(P.begin(), P.end()) : 0;
   b->t.sweep_blocks = ss[nd];
   b->t.claim_blocks = cs[nd];
   b->t.commit_blocks = ms[nd];

@@ -15,20 +15,29 @@
 // Forces are gathered per sphere (each sphere sums over its own partners), so
 // nothing is scattered and the pair terms come out antisymmetric exactly.
 //
-// Two kernels.  Few spheres: one workgroup, sub-cycles separated by workgroup
-// barriers (with state, histories and lists in LDS up to DEM_LDS_MAX spheres).
-// Many spheres: one thread per sphere over a chain of launches; neighbours
-// are found through uniform bins, and x, u, w alternate between two buffers
-// every sub-cycle (positions are advanced into the other buffer, then forces
-// read the new positions and the old velocities and write the new velocities
-// into the other buffer), so each sub-cycle needs only two launches.
+// Few spheres: one workgroup, eight lanes per sphere, state in LDS, sub-cycles
+// separated by workgroup barriers (beyond DEM_LDS_MAX spheres, where it is asked
+// for explicitly, one thread per sphere on global memory).  Many spheres: eight
+// lanes per sphere over a chain of launches; neighbours are found through
+// uniform bins, and x, u, w alternate between two buffers every sub-cycle
+// (positions are advanced into the other buffer, then forces read the new
+// positions and the old velocities and write the new velocities into the other
+// buffer), so each sub-cycle needs only two launches.  All give the same bits.
 #include "internal.hpp"
 
+#include <algorithm>
 #include <climits>
 
 namespace lbmdem {
 
 constexpr double PI_D = 3.14159265358979323846;
+
+// one of three values (all read first: choosing between fields of the
+// by-value descriptor would place it in scratch memory)
+template <typename T>
+__device__ __forceinline__ T sel3(int k, T a, T b, T c) {
+  return k == 0 ? a : (k == 1 ? b : c);
+}
 
 struct Partner {
   int code;        // sphere id >= 0, wall -1 - (2 axis + side)
@@ -58,24 +67,37 @@ __device__ inline void body_vel(const double* u, const double* w, const double* 
   U[2] = u[2] + wr[2];
 }
 
-__device__ __forceinline__ void make_sphere_partner(const DevDomain& d, const DevParticles& p, int i, int j,
-                                                    Partner& pt) {
-  double dd[3];
+// sphere partner at xj: gap first (most listed partners are out of reach), the
+// rest of the geometry on demand
+__device__ __forceinline__ double sphere_offset(const DevDomain& d, const double* xi, double Ri, const double* xj,
+                                                double Rj, double* dd, double* dist) {
   const int n[3] = {d.nx, d.ny, d.nz};
-  for (int a = 0; a < 3; ++a) dd[a] = min_image(p.x[3 * i + a] - p.x[3 * j + a], n[a], d.walls[a]);
-  const double dist = norm3(dd);
+  for (int a = 0; a < 3; ++a) dd[a] = min_image(xi[a] - xj[a], n[a], d.walls[a]);
+  *dist = norm3(dd);
+  return *dist - (Ri + Rj);
+}
+
+__device__ __forceinline__ void make_sphere_partner(const double* xi, int j, const double* dd, double dist,
+                                                    double delta, Partner& pt) {
   pt.code = j;
   pt.j = j;
-  for (int a = 0; a < 3; ++a) pt.n[a] = dd[a] / dist;
-  pt.delta = dist - (p.R[i] + p.R[j]);
+  pt.delta = delta;
   for (int a = 0; a < 3; ++a) {
-    pt.xcp[a] = p.x[3 * i + a] - 0.5 * dd[a];
+    pt.n[a] = dd[a] / dist;
+    pt.xcp[a] = xi[a] - 0.5 * dd[a];
     pt.rj[a] = 0.5 * dd[a];
   }
 }
 
-__device__ __forceinline__ void make_wall_partner(const DevDomain& d, const DevParticles& p, int i, int a,
-                                                  int side, Partner& pt) {
+// gap to the wall plane of an axis and side
+__device__ __forceinline__ double wall_gap(const DevDomain& d, const double* xi, double R, int a, int side) {
+  const double xa = sel3(a, xi[0], xi[1], xi[2]);
+  const int na = sel3(a, d.nx, d.ny, d.nz);
+  return side ? (((double)na - 1.0) - xa) - R : (xa - 1.0) - R;
+}
+
+__device__ __forceinline__ void make_wall_partner(const double* xi, double R, int a, int side, double delta,
+                                                  Partner& pt) {
   // selects instead of indexing local arrays with the runtime axis, so that
   // nothing spills to scratch memory
   const double s = side ? -1.0 : 1.0;
@@ -84,16 +106,17 @@ __device__ __forceinline__ void make_wall_partner(const DevDomain& d, const DevP
   pt.n[0] = a == 0 ? s : 0.0;
   pt.n[1] = a == 1 ? s : 0.0;
   pt.n[2] = a == 2 ? s : 0.0;
-  const double R = p.R[i];
-  const double x0 = p.x[3 * i], x1 = p.x[3 * i + 1], x2 = p.x[3 * i + 2];
-  const double xa = a == 0 ? x0 : (a == 1 ? x1 : x2);
-  const int na = a == 0 ? d.nx : (a == 1 ? d.ny : d.nz);
-  pt.delta = side ? (((double)na - 1.0) - xa) - R : (xa - 1.0) - R;
-  const double h = R + 0.5 * pt.delta;
-  pt.xcp[0] = x0 - h * pt.n[0];
-  pt.xcp[1] = x1 - h * pt.n[1];
-  pt.xcp[2] = x2 - h * pt.n[2];
+  pt.delta = delta;
+  const double h = R + 0.5 * delta;
+  for (int k = 0; k < 3; ++k) pt.xcp[k] = xi[k] - h * pt.n[k];
   pt.rj[0] = pt.rj[1] = pt.rj[2] = 0.0;
+}
+
+// axis and side of the wk-th wall plane (walled axes in order, lower side first)
+__device__ __forceinline__ void wall_of(const DevDomain& d, int wk, int* a, int* side) {
+  const int w0 = d.walls[0] ? 2 : 0, w1 = d.walls[1] ? 2 : 0;
+  *a = wk < w0 ? 0 : (wk < w0 + w1 ? 1 : 2);
+  *side = wk - (*a == 0 ? 0 : (*a == 1 ? w0 : w0 + w1));
 }
 
 __device__ inline double collision_time(const DevDomain& d, double D) {
@@ -155,198 +178,362 @@ __device__ __forceinline__ void lubrication(const DevDomain& d, double dmin, con
   }
 }
 
-// forces on sphere i at the current state; contact: evaluate contacts;
-// upd: write the tangential-spring history
+__device__ __forceinline__ double longest_cut(const DevDomain& d) {
+  return fmax(d.cut_n, fmax(d.cut_tt, d.cut_tr));
+}
+
+// What one partner does to sphere i: c[0..2] lubrication force, c[3..5] its
+// torque, c[6..8] contact force, c[9..11] its torque.  hv: the pair's
+// tangential spring (zero for a new contact); returns whether the two touch
+// (and contacts are evaluated), with the new spring in hv.
+__device__ __forceinline__ bool pair_terms(const DevDomain& d, bool contact, const Partner& pt, const double* xi,
+                                           const double* ui, const double* wi, double Ri, double mi,
+                                           const double* uj, const double* wj, double Rj, double mj, double dtp,
+                                           double* hv, double* c) {
+  const bool is_wall = pt.j < 0;
+  const bool touch = contact && pt.delta < 0.0;
+  if (touch) {
+    double uij[3], un[3], Ui[3], Uj[3], ut[3], ri[3];
+    for (int a = 0; a < 3; ++a) {
+      uij[a] = ui[a] - uj[a];
+      ri[a] = pt.xcp[a] - xi[a];
+    }
+    const double uijn = dot3(uij, pt.n);
+    for (int a = 0; a < 3; ++a) un[a] = uijn * pt.n[a];
+    body_vel(ui, wi, ri, Ui);
+    if (is_wall) {
+      Uj[0] = Uj[1] = Uj[2] = 0.0;
+    } else {
+      body_vel(uj, wj, pt.rj, Uj);
+    }
+    for (int a = 0; a < 3; ++a) ut[a] = (Ui[a] - Uj[a]) - un[a];
+    const double meff = is_wall ? mi : mi * mj / (mi + mj);
+    const double D = is_wall ? 2.0 * Ri : Ri + Rj;
+    const double Tc = collision_time(d, D);
+    const double le = log(d.e_dry);
+    const double kn = meff * (PI_D * PI_D + le * le) / (Tc * Tc);  // Eq. (normalDEMparameters)
+    const double dn = -2.0 * meff * le / Tc;
+    const double kp = 2.0 * (1.0 - d.poisson_ratio) / (2.0 - d.poisson_ratio);
+    const double kt = kp * kn;  // Eq. (tangentialCollisionParameters)
+    const double dt = sqrt(kp) * dn;
+    double Fn[3];
+    for (int a = 0; a < 3; ++a) Fn[a] = -kn * pt.delta * pt.n[a] - dn * un[a];
+    const double hn = dot3(hv, pt.n);
+    double ht[3];
+    for (int a = 0; a < 3; ++a) ht[a] = hv[a] - hn * pt.n[a];
+    const double lh = norm3(hv), lht = norm3(ht);
+    if (lht > 0.0)
+      for (int a = 0; a < 3; ++a) hv[a] = (lh / lht) * ht[a];
+    else
+      for (int a = 0; a < 3; ++a) hv[a] = ht[a];
+    double Fsd[3];
+    for (int a = 0; a < 3; ++a) Fsd[a] = -kt * hv[a] - dt * ut[a];
+    const double fsd = norm3(Fsd);
+    const double fmax = d.friction * norm3(Fn);
+    double Ft[3];
+    if (fsd < fmax || fsd == 0.0) {
+      for (int a = 0; a < 3; ++a) {
+        Ft[a] = Fsd[a];
+        hv[a] = hv[a] + dtp * ut[a];
+      }
+    } else {
+      for (int a = 0; a < 3; ++a) {
+        const double tv = Fsd[a] / fsd;
+        Ft[a] = fmax * tv;
+        hv[a] = -(fmax * tv + dt * ut[a]) / kt;
+      }
+    }
+    double Tt[3];
+    cross3(ri, Ft, Tt);
+    for (int a = 0; a < 3; ++a) {
+      c[6 + a] += Fn[a] + Ft[a];
+      c[9 + a] += Tt[a];
+    }
+  }
+  if (pt.delta > 0.0 && pt.delta < longest_cut(d)) {
+    const double Rh = is_wall ? Ri : 2.0 * Ri * Rj / (Ri + Rj);
+    lubrication(d, min_lub_gap(d, Rh), pt.n, pt.delta, ui, wi, Ri, uj, wj, Rj, is_wall, c, c + 3);
+  }
+  return touch;
+}
+
+// total force (k < 3) or torque component from the partner sums
+__device__ __forceinline__ double total_term(double ffp, double lub, double col, double fext, bool force) {
+  return force ? ((ffp + lub) + col) + fext : (ffp + lub) + col;
+}
+
+// V (rho_p - rho_f), the mass the external force acts on
+__device__ __forceinline__ double buoyant_mass(double R, double rho) {
+  const double V = (4.0 / 3.0) * PI_D * R * R * R;
+  return V * (rho - 1.0);
+}
+
+// forces on sphere i at the current state, one thread: the terms of its
+// partners, each formed from zero, added in list order (neighbours, then
+// walls).  contact: evaluate contacts; upd: write the tangential-spring
+// history
 __device__ __forceinline__ void eval_forces(const DevDomain& d, const DevParticles& p, int i, bool contact,
                                             bool upd, double dtp, double* Fout, double* Tout) {
-  double Flub[3] = {0, 0, 0}, Tlub[3] = {0, 0, 0}, Fcol[3] = {0, 0, 0}, Tcol[3] = {0, 0, 0};
-  const double maxcut = fmax(d.cut_n, fmax(d.cut_tt, d.cut_tr));
-  const double* xi = p.x + 3 * i;
-  const double* ui = p.u + 3 * i;
-  const double* wi = p.w + 3 * i;
+  double sum[12] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+  const double maxcut = longest_cut(d);
+  const double xi[3] = {p.x[3 * i], p.x[3 * i + 1], p.x[3 * i + 2]};
+  const double ui[3] = {p.u[3 * i], p.u[3 * i + 1], p.u[3 * i + 2]};
+  const double wi[3] = {p.w[3 * i], p.w[3 * i + 1], p.w[3 * i + 2]};
   const double Ri = p.R[i];
   int* hid = p.hist_id + (size_t)i * HIST_SLOTS;
   double* hd = p.hist_d + (size_t)i * HIST_SLOTS * 3;
   const int nn = p.nbr_n[i];
   const int nwalls = 2 * (d.walls[0] + d.walls[1] + d.walls[2]);
-  const double zero[3] = {0, 0, 0};
+  bool any = false;
+  for (int s = 0; s < HIST_SLOTS; ++s) any = any || hid[s] != INT_MIN;
   for (int pi = 0; pi < nn + nwalls; ++pi) {
-    Partner pt;
-    if (pi < nn) {
-      make_sphere_partner(d, p, i, p.nbr[(size_t)i * NBR_MAX + pi], pt);
+    const bool wall = pi >= nn;
+    int j = -1, a = 0, side = 0;
+    double dd[3] = {0, 0, 0}, dist = 0.0, delta;
+    if (!wall) {
+      j = p.nbr[(size_t)i * NBR_MAX + pi];
+      delta = sphere_offset(d, xi, Ri, p.x + 3 * j, p.R[j], dd, &dist);
     } else {
-      int wk = pi - nn, a = 0;
-      for (a = 0; a < 3; ++a) {
-        if (!d.walls[a]) continue;
-        if (wk < 2) break;
-        wk -= 2;
-      }
-      make_wall_partner(d, p, i, a, wk, pt);
+      wall_of(d, pi - nn, &a, &side);
+      delta = wall_gap(d, xi, Ri, a, side);
     }
-    const bool is_wall = pt.j < 0;
-    const double* uj = is_wall ? zero : p.u + 3 * pt.j;
-    const double* wj = is_wall ? zero : p.w + 3 * pt.j;
-    const double Rj = is_wall ? 0.0 : p.R[pt.j];
+    const int code = wall ? -1 - (2 * a + side) : j;
     int slot = -1;
-    for (int s = 0; s < HIST_SLOTS; ++s)
-      if (hid[s] == pt.code) slot = s;
-    if (contact && pt.delta < 0.0) {
-      double uij[3], un[3], Ui[3], Uj[3], ut[3], ri[3];
-      for (int a = 0; a < 3; ++a) {
-        uij[a] = ui[a] - uj[a];
-        ri[a] = pt.xcp[a] - xi[a];
-      }
-      const double uijn = dot3(uij, pt.n);
-      for (int a = 0; a < 3; ++a) un[a] = uijn * pt.n[a];
-      body_vel(ui, wi, ri, Ui);
-      if (is_wall) {
-        Uj[0] = Uj[1] = Uj[2] = 0.0;
+    if (any)
+      for (int s = 0; s < HIST_SLOTS; ++s)
+        if (hid[s] == code) slot = s;
+    if (!(delta < maxcut) && slot < 0) continue;
+    Partner pt;
+    if (wall)
+      make_wall_partner(xi, Ri, a, side, delta, pt);
+    else
+      make_sphere_partner(xi, j, dd, dist, delta, pt);
+    const double zero[3] = {0, 0, 0};
+    const double* uj = wall ? zero : p.u + 3 * j;
+    const double* wj = wall ? zero : p.w + 3 * j;
+    double hv[3] = {0, 0, 0}, c[12] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    if (slot >= 0)
+      for (int k = 0; k < 3; ++k) hv[k] = hd[slot * 3 + k];
+    const bool touch = pair_terms(d, contact, pt, xi, ui, wi, Ri, p.m[i], uj, wj, wall ? 0.0 : p.R[j],
+                                  wall ? 0.0 : p.m[j], dtp, hv, c);
+    if (upd && touch) {
+      if (slot < 0)
+        for (int s = 0; s < HIST_SLOTS && slot < 0; ++s)
+          if (hid[s] == INT_MIN) slot = s;
+      if (slot < 0) {
+        atomicOr(d.status, ST_HIST_FULL);
       } else {
-        body_vel(uj, wj, pt.rj, Uj);
-      }
-      for (int a = 0; a < 3; ++a) ut[a] = (Ui[a] - Uj[a]) - un[a];
-      const double mi = p.m[i];
-      const double meff = is_wall ? mi : mi * p.m[pt.j] / (mi + p.m[pt.j]);
-      const double D = is_wall ? 2.0 * Ri : Ri + Rj;
-      const double Tc = collision_time(d, D);
-      const double le = log(d.e_dry);
-      const double kn = meff * (PI_D * PI_D + le * le) / (Tc * Tc);  // Eq. (normalDEMparameters)
-      const double dn = -2.0 * meff * le / Tc;
-      const double kp = 2.0 * (1.0 - d.poisson_ratio) / (2.0 - d.poisson_ratio);
-      const double kt = kp * kn;  // Eq. (tangentialCollisionParameters)
-      const double dt = sqrt(kp) * dn;
-      double Fn[3];
-      for (int a = 0; a < 3; ++a) Fn[a] = -kn * pt.delta * pt.n[a] - dn * un[a];
-      double hv[3] = {0, 0, 0};
-      if (slot >= 0)
-        for (int a = 0; a < 3; ++a) hv[a] = hd[slot * 3 + a];
-      const double hn = dot3(hv, pt.n);
-      double ht[3];
-      for (int a = 0; a < 3; ++a) ht[a] = hv[a] - hn * pt.n[a];
-      const double lh = norm3(hv), lht = norm3(ht);
-      if (lht > 0.0)
-        for (int a = 0; a < 3; ++a) hv[a] = (lh / lht) * ht[a];
-      else
-        for (int a = 0; a < 3; ++a) hv[a] = ht[a];
-      double Fsd[3];
-      for (int a = 0; a < 3; ++a) Fsd[a] = -kt * hv[a] - dt * ut[a];
-      const double fsd = norm3(Fsd);
-      const double fmax = d.friction * norm3(Fn);
-      double Ft[3], hnew[3];
-      if (fsd < fmax || fsd == 0.0) {
-        for (int a = 0; a < 3; ++a) {
-          Ft[a] = Fsd[a];
-          hnew[a] = hv[a] + dtp * ut[a];
-        }
-      } else {
-        for (int a = 0; a < 3; ++a) {
-          const double tv = Fsd[a] / fsd;
-          Ft[a] = fmax * tv;
-          hnew[a] = -(fmax * tv + dt * ut[a]) / kt;
-        }
-      }
-      double Tt[3];
-      cross3(ri, Ft, Tt);
-      for (int a = 0; a < 3; ++a) {
-        Fcol[a] += Fn[a] + Ft[a];
-        Tcol[a] += Tt[a];
-      }
-      if (upd) {
-        if (slot < 0)
-          for (int s = 0; s < HIST_SLOTS && slot < 0; ++s)
-            if (hid[s] == INT_MIN) slot = s;
-        if (slot < 0) {
-          atomicOr(d.status, ST_HIST_FULL);
-        } else {
-          hid[slot] = pt.code;
-          for (int a = 0; a < 3; ++a) hd[slot * 3 + a] = hnew[a];
-        }
+        hid[slot] = code;
+        any = true;
+        for (int k = 0; k < 3; ++k) hd[slot * 3 + k] = hv[k];
       }
     } else if (upd && slot >= 0) {
       hid[slot] = INT_MIN;
     }
-    if (pt.delta > 0.0 && pt.delta < maxcut) {
-      const double Rh = is_wall ? Ri : 2.0 * Ri * Rj / (Ri + Rj);
-      lubrication(d, min_lub_gap(d, Rh), pt.n, pt.delta, ui, wi, Ri, uj, wj, Rj, is_wall, Flub, Tlub);
-    }
+    for (int k = 0; k < 12; ++k) sum[k] += c[k];
   }
-  const double V = (4.0 / 3.0) * PI_D * Ri * Ri * Ri;
+  const double bm = buoyant_mass(Ri, p.rho[i]);
   const double* Ffp = p.Ffp + 6 * i;
   double* dg = p.diag + 18 * i;
   for (int a = 0; a < 3; ++a) {
-    const double Fext = V * (p.rho[i] - 1.0) * d.gravity[a];
-    Fout[a] = ((Ffp[a] + Flub[a]) + Fcol[a]) + Fext;
-    Tout[a] = (Ffp[3 + a] + Tlub[a]) + Tcol[a];
-    dg[6 + a] = Flub[a];
-    dg[9 + a] = Tlub[a];
-    dg[12 + a] = Fcol[a];
-    dg[15 + a] = Tcol[a];
+    Fout[a] = total_term(Ffp[a], sum[a], sum[6 + a], bm * d.gravity[a], true);
+    Tout[a] = total_term(Ffp[3 + a], sum[3 + a], sum[9 + a], 0.0, false);
   }
+  for (int k = 0; k < 12; ++k) dg[6 + k] = sum[k];
+}
+
+// ---- eight lanes per sphere --------------------------------------------------
+// The sub-cycles are chains of dependent FP64 work and memory round trips, so
+// the partners of a sphere are taken by the eight lanes of a group at once:
+// lane g forms the terms of partners g, g + 8, ..., and the terms of those in
+// reach are then added in list order (shuffles over the set bits of the
+// group's ballot), the same order and bits as eval_forces.  The group's lanes
+// 0-2 and 3-5 hold the components of force, velocity and torque, spin.
+constexpr int GROUP = 8;
+
+// state arrays of the spheres, in LDS or in global memory
+struct GroupState {
+  const double *x, *u, *w;  // [P][3]
+  const double *R, *m;      // [P]
+};
+
+// Sums of the terms of all partners of sphere i: component g (< 6) of the
+// lubrication and of the contact force and torque into *lub and *col of lane
+// g; nbr(k): the k-th listed neighbour.  Every lane of the wavefront
+// calls it (`on`: the group has a sphere).  hid: the sphere's 24 history codes;
+// hd: its springs.
+template <typename NBR>
+__device__ __forceinline__ void group_forces(const DevDomain& d, const GroupState& s, int i, bool on, int nn,
+                                             NBR nbr, int* hid, double* hd, bool contact, bool upd, double dtp,
+                                             double* lub, double* col) {
+  const int lane = threadIdx.x & 63, g = lane & (GROUP - 1), base = lane & ~(GROUP - 1);
+  const double maxcut = longest_cut(d);
+  double xi[3] = {0, 0, 0}, Ri = 0.0;
+  bool h = false;
+  if (on) {
+    for (int a = 0; a < 3; ++a) xi[a] = s.x[3 * i + a];
+    Ri = s.R[i];
+#pragma unroll
+    for (int k = 0; k < HIST_SLOTS / GROUP; ++k) h = h || hid[g + GROUP * k] != INT_MIN;
+  }
+  const bool any = ((__ballot(h) >> base) & 0xFFull) != 0;  // the sphere has a spring
+  const int nwalls = 2 * (d.walls[0] + d.walls[1] + d.walls[2]);
+  const int tot = on ? nn + nwalls : 0;
+  double sl = 0.0, sc = 0.0;
+  for (int p0 = 0; __any(p0 < tot); p0 += GROUP) {
+    const int pi = p0 + g;
+    double c[12] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    bool reach = false;
+    if (pi < tot) {
+      const bool wall = pi >= nn;
+      int j = -1, a = 0, side = 0;
+      double dd[3] = {0, 0, 0}, dist = 0.0, delta, Rj = 0.0;
+      if (!wall) {
+        j = nbr(pi);
+        Rj = s.R[j];
+        delta = sphere_offset(d, xi, Ri, s.x + 3 * j, Rj, dd, &dist);
+      } else {
+        wall_of(d, pi - nn, &a, &side);
+        delta = wall_gap(d, xi, Ri, a, side);
+      }
+      const int code = wall ? -1 - (2 * a + side) : j;
+      int slot = -1;
+      if (any)
+        for (int q = 0; q < HIST_SLOTS; ++q)
+          if (hid[q] == code) slot = q;
+      reach = delta < maxcut || slot >= 0;
+      if (reach) {
+        Partner pt;
+        if (wall)
+          make_wall_partner(xi, Ri, a, side, delta, pt);
+        else
+          make_sphere_partner(xi, j, dd, dist, delta, pt);
+        double ui[3], wi[3], uj[3] = {0, 0, 0}, wj[3] = {0, 0, 0}, hv[3] = {0, 0, 0}, mj = 0.0;
+        for (int q = 0; q < 3; ++q) {
+          ui[q] = s.u[3 * i + q];
+          wi[q] = s.w[3 * i + q];
+        }
+        if (!wall) {
+          for (int q = 0; q < 3; ++q) {
+            uj[q] = s.u[3 * j + q];
+            wj[q] = s.w[3 * j + q];
+          }
+          mj = s.m[j];
+        }
+        if (slot >= 0)
+          for (int q = 0; q < 3; ++q) hv[q] = hd[slot * 3 + q];
+        const bool touch = pair_terms(d, contact, pt, xi, ui, wi, Ri, s.m[i], uj, wj, Rj, mj, dtp, hv, c);
+        if (upd && touch) {
+          // a free slot: lanes of a group may look for one at the same time
+          for (int q = 0; q < HIST_SLOTS && slot < 0; ++q)
+            if (atomicCAS(hid + q, INT_MIN, code) == INT_MIN) slot = q;
+          if (slot < 0) {
+            atomicOr(d.status, ST_HIST_FULL);
+          } else {
+            for (int q = 0; q < 3; ++q) hd[slot * 3 + q] = hv[q];
+          }
+        } else if (upd && slot >= 0) {
+          hid[slot] = INT_MIN;
+        }
+      }
+    }
+    unsigned in = (unsigned)((__ballot(reach) >> base) & 0xFFull);
+    while (__any(in != 0)) {
+      const int src = in ? base + __ffs(in) - 1 : lane;
+#pragma unroll
+      for (int k = 0; k < 6; ++k) {
+        const double vl = __shfl(c[k], src, 64), vc = __shfl(c[6 + k], src, 64);
+        if (in && g == k) {
+          sl += vl;
+          sc += vc;
+        }
+      }
+      in &= in - 1u;
+    }
+  }
+  *lub = sl;
+  *col = sc;
+}
+
+// component g (< 6) of the total force or torque
+__device__ __forceinline__ double group_total(const DevDomain& d, int g, double lub, double col, double ffp,
+                                              double bm) {
+  const double grav = sel3(g, d.gravity[0], d.gravity[1], d.gravity[2]);
+  return total_term(ffp, lub, col, bm * grav, g < 3);
 }
 
 // Momentum-exchange sum of sphere i by one wavefront: lane l adds the
 // partials l, l + 64, ... in order, then a fixed shuffle tree combines the
-// lanes, so the result does not depend on scheduling.  Lane 0 then averages
-// with the previous step and pins the positions the mapping starts from.
-__device__ __forceinline__ void resolved_force(const DevDomain& d, const DevParticles& p, int i, int lane) {
+// lanes, so the result does not depend on scheduling.  Lane c < 6 then averages
+// its component with the previous step (into Ffp, and copy if given), and lanes
+// 0-2 pin the position the mapping starts from.  (Everything the wave needs is
+// loaded before the tree: one memory round trip; the tree's steps stay a loop:
+// beside the sweep every new line of code is a fetch of its own.)
+__device__ __forceinline__ void resolved_force(const DevDomain& d, const DevParticles& p, int i, int lane,
+                                               double* copy = nullptr) {
   const int nb = d.ZB * d.RB;
+  const int c = lane < 6 ? lane : 0;
+  double prev = p.Fprev[6 * i + c];
+  const double x = p.x[3 * i + (lane < 3 ? lane : 0)];
+  const bool valid = p.prev_valid[i] != 0;
   double F[6] = {0, 0, 0, 0, 0, 0};
   for (int b = lane; b < nb; b += 64)
     for (int k = 0; k < 6; ++k) F[k] += d.partial[((size_t)i * nb + b) * 6 + k];
+#pragma unroll 1
+  for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+    for (int k = 0; k < 6; ++k) F[k] += __shfl_down(F[k], off, 64);
+  double f = 0.0;
+#pragma unroll
   for (int k = 0; k < 6; ++k) {
-    double v = F[k];
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-    F[k] = v;
+    const double v = __shfl(F[k], 0, 64);
+    if (lane == k) f = v;
   }
-  if (lane != 0) return;
-  for (int k = 0; k < 6; ++k) p.Fraw[6 * i + k] = F[k];
+  if (lane >= 6) return;
+  const int k = 6 * i + lane;
+  p.Fraw[k] = f;
+  double m = f;
   if (d.force_averaging) {
-    if (!p.prev_valid[i])
-      for (int k = 0; k < 6; ++k) p.Fprev[6 * i + k] = F[k];
-    for (int k = 0; k < 6; ++k) {
-      p.Ffp[6 * i + k] = 0.5 * (F[k] + p.Fprev[6 * i + k]);
-      p.Fprev[6 * i + k] = F[k];
-    }
-    p.prev_valid[i] = 1;
-  } else {
-    for (int k = 0; k < 6; ++k) p.Ffp[6 * i + k] = F[k];
+    if (!valid) prev = f;
+    m = 0.5 * (f + prev);
+    p.Fprev[k] = f;
+    if (lane == 0) p.prev_valid[i] = 1;
   }
-  for (int a = 0; a < 3; ++a) p.xmap[3 * i + a] = p.x[3 * i + a];
+  p.Ffp[k] = m;
+  if (copy) copy[k] = m;
+  if (lane < 3) p.xmap[3 * i + lane] = x;
 }
 
-// gap between spheres i and j (minimum image); the neighbour test of both
+// gap between spheres i and j (minimum image); the neighbour test of all
 // kernels, so that they list the same partners
 __device__ __forceinline__ double pair_gap(const DevDomain& d, const DevParticles& p, int i, int j) {
-  const int n[3] = {d.nx, d.ny, d.nz};
-  double dd[3];
-  for (int a = 0; a < 3; ++a) dd[a] = min_image(p.x[3 * i + a] - p.x[3 * j + a], n[a], d.walls[a]);
-  return norm3(dd) - (p.R[i] + p.R[j]);
+  double dd[3], dist;
+  return sphere_offset(d, p.x + 3 * i, p.R[i], p.x + 3 * j, p.R[j], dd, &dist);
 }
 
 __device__ __forceinline__ double list_range(const DevDomain& d) {
-  return fmax(d.cut_n, fmax(d.cut_tt, d.cut_tr)) + d.skin;
+  return longest_cut(d) + d.skin;
 }
 
 // Gap of a prescribed sphere to the wall plane it approaches: the plane ahead
 // along its target velocity on every walled axis where that is nonzero
 // (Sec. 4.4.2 switches the acceleration off near the wall the sphere moves
 // to); large if there is none.
-__device__ inline double gap_ahead(const DevDomain& d, const DevParticles& p, int i) {
+__device__ __forceinline__ double axis_gap_ahead(double x, double R, double ut, int wall, double n) {
+  if (!wall || ut == 0.0) return 1e300;
+  return ut < 0.0 ? (x - 1.0) - R : ((n - 1.0) - x) - R;
+}
+__device__ inline double gap_ahead(const DevDomain& d, const double* x, double R, const double* presc) {
   double g = 1e300;
   const int n[3] = {d.nx, d.ny, d.nz};
 #pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    const double ut = p.presc[6 * i + a];
-    if (!d.walls[a] || ut == 0.0) continue;
-    const double v = ut < 0.0 ? (p.x[3 * i + a] - 1.0) - p.R[i] : (((double)n[a] - 1.0) - p.x[3 * i + a]) - p.R[i];
-    g = fmin(g, v);
-  }
+  for (int a = 0; a < 3; ++a) g = fmin(g, axis_gap_ahead(x[a], R, presc[a], d.walls[a], (double)n[a]));
   return g;
 }
 
 // release of a prescribed sphere below its gap; start force of a newly free one
 __device__ __forceinline__ void release_and_start(const DevDomain& d, const DevParticles& p, int i, double dtp) {
-  if (p.mode[i] == MODE_PRESCRIBED && gap_ahead(d, p, i) < p.presc[6 * i + 5]) {
+  if (p.mode[i] == MODE_PRESCRIBED && gap_ahead(d, p.x + 3 * i, p.R[i], p.presc + 6 * i) < p.presc[6 * i + 5]) {
     p.mode[i] = MODE_FREE;
     p.old_valid[i] = 0;
   }
@@ -356,51 +543,68 @@ __device__ __forceinline__ void release_and_start(const DevDomain& d, const DevP
   }
 }
 
-// Eq. (velocity_verlet_1) (free), x + dt_p u (prescribed), unchanged (fixed);
-// periodic axes wrap.  xo may alias p.x + 3 i.
+// Factors of Eqs. (velocity_verlet_1) and (velocity_verlet_2) of a mass (or
+// moment of inertia) m
+__device__ __forceinline__ double position_factor(double m, double dtp) { return dtp * dtp / (2.0 * m); }
+__device__ __forceinline__ double velocity_factor(double m, double dtp) { return dtp / (2.0 * m); }
+
+// One component of Eq. (velocity_verlet_1) (free), x + dt_p u (prescribed),
+// unchanged (fixed); periodic axes wrap
+__device__ __forceinline__ double next_position(int mode, double x, double u, double fold, double c2, double dtp,
+                                                double L, int wall) {
+  double xo = x;
+  if (mode == MODE_FREE)
+    xo = (x + dtp * u) + c2 * fold;
+  else if (mode == MODE_PRESCRIBED)
+    xo = x + dtp * u;
+  if (!wall) {
+    if (xo < 0.0)
+      xo += L;
+    else if (xo >= L)
+      xo -= L;
+  }
+  return xo;
+}
+
+// one component of Eq. (velocity_verlet_2) or its rotational analogue
+__device__ __forceinline__ double next_velocity(double v, double fold, double fnew, double cu) {
+  return v + cu * (fold + fnew);
+}
+
+// the ramp of Eq. (artificial_acceleration)
+__device__ __forceinline__ double prescribed_velocity(double u_target, double c_acc, double t_st, double t) {
+  const double ramp = 1.0 - exp(-c_acc * t / t_st);
+  return u_target * ramp;
+}
+
+// the position of sphere i after a sub-cycle; xo may alias p.x + 3 i
 __device__ __forceinline__ void advance_position(const DevDomain& d, const DevParticles& p, int i, double dtp,
                                                  double* xo) {
   const int n[3] = {d.nx, d.ny, d.nz};
-  const double* x = p.x + 3 * i;
-  if (p.mode[i] == MODE_FREE) {
-    const double c2 = dtp * dtp / (2.0 * p.m[i]);
-    for (int a = 0; a < 3; ++a) xo[a] = (x[a] + dtp * p.u[3 * i + a]) + c2 * p.Fold[6 * i + a];
-  } else if (p.mode[i] == MODE_PRESCRIBED) {
-    for (int a = 0; a < 3; ++a) xo[a] = x[a] + dtp * p.u[3 * i + a];
-  } else {
-    for (int a = 0; a < 3; ++a) xo[a] = x[a];
-  }
-  for (int a = 0; a < 3; ++a) {
-    if (d.walls[a]) continue;
-    const double L = (double)n[a];
-    if (xo[a] < 0.0)
-      xo[a] += L;
-    else if (xo[a] >= L)
-      xo[a] -= L;
-  }
+  for (int a = 0; a < 3; ++a)
+    xo[a] = next_position(p.mode[i], p.x[3 * i + a], p.u[3 * i + a], p.Fold[6 * i + a],
+                          position_factor(p.m[i], dtp), dtp, (double)n[a],
+                          d.walls[a]);
 }
 
-// Eq. (velocity_verlet_2) and its rotational analogue from F_old and the new
-// force in p.Fnew; the ramp of Eq. (artificial_acceleration) for prescribed
-// spheres.  uo, wo may alias p.u + 3 i, p.w + 3 i.
+// velocities of sphere i from F_old and the new force in p.Fnew; uo, wo may
+// alias p.u + 3 i, p.w + 3 i.
 __device__ __forceinline__ void advance_velocity(const DevDomain& d, const DevParticles& p, int i, double dtp,
                                                  double* uo, double* wo) {
   const double* Fn = p.Fnew + 6 * i;
   double* dg = p.diag + 18 * i;
   for (int k = 0; k < 6; ++k) dg[k] = Fn[k];
   if (p.mode[i] == MODE_FREE) {
-    const double cu = dtp / (2.0 * p.m[i]), cw = dtp / (2.0 * p.I[i]);
     for (int a = 0; a < 3; ++a) {
-      uo[a] = p.u[3 * i + a] + cu * (p.Fold[6 * i + a] + Fn[a]);
-      wo[a] = p.w[3 * i + a] + cw * (p.Fold[6 * i + 3 + a] + Fn[3 + a]);
+      uo[a] = next_velocity(p.u[3 * i + a], p.Fold[6 * i + a], Fn[a], velocity_factor(p.m[i], dtp));
+      wo[a] = next_velocity(p.w[3 * i + a], p.Fold[6 * i + 3 + a], Fn[3 + a], velocity_factor(p.I[i], dtp));
       p.Fold[6 * i + a] = Fn[a];
       p.Fold[6 * i + 3 + a] = Fn[3 + a];
     }
   } else if (p.mode[i] == MODE_PRESCRIBED) {
     p.tpresc[i] += dtp;
-    const double ramp = 1.0 - exp(-p.presc[6 * i + 3] * p.tpresc[i] / p.presc[6 * i + 4]);
     for (int a = 0; a < 3; ++a) {
-      uo[a] = p.presc[6 * i + a] * ramp;
+      uo[a] = prescribed_velocity(p.presc[6 * i + a], p.presc[6 * i + 3], p.presc[6 * i + 4], p.tpresc[i]);
       wo[a] = 0.0;
     }
   } else {
@@ -480,106 +684,206 @@ __global__ __launch_bounds__(256) void k_dem(DevDomain d) {
   dem_global_run(d);
 }
 
-// Few spheres: their state, contact histories and neighbour lists live in LDS
-// for the whole step, so the sub-cycles (separated by workgroup barriers) do
-// not wait on memory round trips.
-constexpr int DEM_LDS_MAX = 32;
-
-__device__ __forceinline__ void dem_lds_run(const DevDomain& d) {
-  constexpr int PS = DEM_LDS_MAX;
-  __shared__ double sx[3 * PS], su[3 * PS], sw[3 * PS], sR[PS], sm[PS], sI[PS], srho[PS], stp[PS];
-  __shared__ double spresc[6 * PS], sFfp[6 * PS], sFold[6 * PS], sdiag[18 * PS], sFnew[6 * PS];
-  __shared__ double shd[3 * HIST_SLOTS * PS];
-  __shared__ int smode[PS], sold[PS], shid[HIST_SLOTS * PS], snbr[NBR_MAX * PS], snn[PS];
-  const int P = d.P;
-  const DevParticles& g = d.p;
-  for (int t = threadIdx.x; t < P; t += blockDim.x) {
-    for (int a = 0; a < 3; ++a) {
-      sx[3 * t + a] = g.x[3 * t + a];
-      su[3 * t + a] = g.u[3 * t + a];
-      sw[3 * t + a] = g.w[3 * t + a];
-    }
-    sR[t] = g.R[t];
-    sm[t] = g.m[t];
-    sI[t] = g.I[t];
-    srho[t] = g.rho[t];
-    stp[t] = g.tpresc[t];
-    smode[t] = g.mode[t];
-    sold[t] = g.old_valid[t];
-    for (int k = 0; k < 6; ++k) {
-      spresc[6 * t + k] = g.presc[6 * t + k];
-      sFold[6 * t + k] = g.Fold[6 * t + k];
-    }
-    for (int k = 0; k < HIST_SLOTS; ++k) {
-      shid[HIST_SLOTS * t + k] = g.hist_id[(size_t)HIST_SLOTS * t + k];
-      for (int a = 0; a < 3; ++a) shd[3 * (HIST_SLOTS * t + k) + a] = g.hist_d[3 * ((size_t)HIST_SLOTS * t + k) + a];
-    }
-  }
-  __syncthreads();
-  DevParticles l = g;
-  l.x = sx;
-  l.u = su;
-  l.w = sw;
-  l.R = sR;
-  l.m = sm;
-  l.I = sI;
-  l.rho = srho;
-  l.presc = spresc;
-  l.tpresc = stp;
-  l.Ffp = sFfp;
-  l.Fold = sFold;
-  l.diag = sdiag;
-  l.Fnew = sFnew;
-  l.mode = smode;
-  l.old_valid = sold;
-  l.hist_id = shid;
-  l.hist_d = shd;
-  l.nbr = snbr;
-  l.nbr_n = snn;
-  dem_body(d, l);
-  __syncthreads();
-  for (int t = threadIdx.x; t < P; t += blockDim.x) {
-    for (int a = 0; a < 3; ++a) {
-      g.x[3 * t + a] = sx[3 * t + a];
-      g.u[3 * t + a] = su[3 * t + a];
-      g.w[3 * t + a] = sw[3 * t + a];
-    }
-    g.tpresc[t] = stp[t];
-    g.mode[t] = smode[t];
-    g.old_valid[t] = sold[t];
-    for (int k = 0; k < 6; ++k) {
-      g.Ffp[6 * t + k] = sFfp[6 * t + k];
-      g.Fold[6 * t + k] = sFold[6 * t + k];
-    }
-    for (int k = 0; k < 18; ++k) g.diag[18 * t + k] = sdiag[18 * t + k];
-    for (int k = 0; k < HIST_SLOTS; ++k) {
-      g.hist_id[(size_t)HIST_SLOTS * t + k] = shid[HIST_SLOTS * t + k];
-      for (int a = 0; a < 3; ++a) g.hist_d[3 * ((size_t)HIST_SLOTS * t + k) + a] = shd[3 * (HIST_SLOTS * t + k) + a];
-    }
-  }
+// Few spheres: one workgroup, a group of eight lanes per sphere.  Lane g < 6 of
+// a group keeps its component of position and velocity (0-2) or spin (3-5) with
+// its force and coefficients in registers for the whole step; what partners
+// read (x, u, w in two buffers, R, m), the histories and the lists live in LDS.
+// Bound by the latency of its dependent FP64 chain, not by any rate.  Against
+// one thread per sphere with the whole state in memory arrays: 1 sphere 37 ->
+// 18 us alone and 93 -> 44 us beside the 128x128x256 FP32 sweep (where every
+// memory access of a sub-cycle costs microseconds: none is left in the quiet
+// path), 40 agitated spheres 253 -> 78 us, 16 requests of a batch 73 -> 27 us.
+// LDS bytes of P spheres
+__host__ __device__ inline size_t dem_lds_bytes(int P) {
+  return (size_t)P * (8 * (3 + 6 + 6 + 6 + 2 + 3 * HIST_SLOTS) + 4 * HIST_SLOTS + NBR_MAX);
 }
+static_assert(DEM_LDS_MAX * (8 * 95 + 4 * HIST_SLOTS + NBR_MAX) <= 65536 && DEM_LDS_MAX <= 255,
+              "few-sphere DEM state exceeds 64 KB of LDS");
+
+__device__ __forceinline__ void dem_lds_run(const DevDomain& d, unsigned char* lds) {
+  const int P = d.P, T = (int)blockDim.x, tid = (int)threadIdx.x;
+  const int g = tid & (GROUP - 1), i = tid / GROUP;  // T >= GROUP P
+  const int lane = tid & 63, base = lane & ~(GROUP - 1);
+  const bool on = i < P, own = on && g < 6;
+  const DevParticles& p = d.p;
+  double* sx = (double*)lds;
+  double *su = sx + 3 * P, *sw = su + 6 * P, *sFfp = sw + 6 * P, *sR = sFfp + 6 * P, *sm = sR + P, *shd = sm + P;
+  int* shid = (int*)(shd + 3 * HIST_SLOTS * P);
+  uint8_t* snbr = (uint8_t*)(shid + HIST_SLOTS * P);
+  __shared__ int s_phase0;
+
+  const double dtp = 1.0 / (double)d.n_sub;
+  const int c = g < 3 ? g : g - 3;  // component of this lane
+  double x = 0.0, v = 0.0, fold = 0.0, cpos = 0.0, cvel = 0.0, fext = 0.0, ut = 0.0, t = 0.0;
+  double c_acc = 0.0, t_st = 1.0, gap = 0.0, R = 0.0;
+  int mode = MODE_FIXED, old = 1;
+  if (tid == 0) s_phase0 = 0;
+  if (on) {
+    const double m = p.m[i], rho = p.rho[i];
+    R = p.R[i];
+    mode = p.mode[i];
+    old = p.old_valid[i];
+    t = p.tpresc[i];
+    if (own) {
+      v = g < 3 ? p.u[3 * i + c] : p.w[3 * i + c];
+      fold = p.Fold[6 * i + g];
+      const double in = g < 3 ? m : p.I[i];
+      if (g < 3) {
+        x = p.x[3 * i + g];
+        ut = p.presc[6 * i + g];
+        fext = buoyant_mass(R, rho) * sel3(g, d.gravity[0], d.gravity[1], d.gravity[2]);
+        sx[3 * i + g] = x;
+        su[3 * i + g] = v;
+      } else {
+        sw[3 * i + c] = v;
+      }
+      cpos = position_factor(m, dtp);
+      cvel = velocity_factor(in, dtp);
+    }
+    if (mode == MODE_PRESCRIBED) {
+      c_acc = p.presc[6 * i + 3];
+      t_st = p.presc[6 * i + 4];
+      gap = p.presc[6 * i + 5];
+    }
+    if (g == 0) {
+      sR[i] = R;
+      sm[i] = m;
+    }
+  }
+  for (int k = tid; k < HIST_SLOTS * P; k += T) shid[k] = p.hist_id[k];
+  for (int k = tid; k < 3 * HIST_SLOTS * P; k += T) shd[k] = p.hist_d[k];
+  // the momentum-exchange sums, one wavefront per sphere
+  for (int k = tid >> 6; k < P; k += T >> 6) resolved_force(d, p, k, lane, sFfp);
+  __syncthreads();
+  const double ffp = own ? sFfp[6 * i + g] : 0.0;
+  if (mode == MODE_PRESCRIBED || (mode == MODE_FREE && !old)) s_phase0 = 1;
+
+  // neighbour list for this step by all pairs, partners ascending
+  int nn = 0;
+  const double range = list_range(d);
+  for (int j0 = 0; j0 < P; j0 += GROUP) {
+    const int j = j0 + g;
+    bool near = false;
+    if (on && j < P && j != i) {
+      double dd[3], dist;
+      near = sphere_offset(d, sx + 3 * i, R, sx + 3 * j, sR[j], dd, &dist) < range;
+    }
+    const unsigned m = (unsigned)((__ballot(near) >> base) & 0xFFull);
+    if (near) {
+      const int at = nn + __popc(m & ((1u << g) - 1u));
+      if (at < NBR_MAX)
+        snbr[NBR_MAX * i + at] = (uint8_t)j;
+      else
+        atomicOr(d.status, ST_NBR_FULL);
+    }
+    nn += __popc(m);
+  }
+  nn = nn < NBR_MAX ? nn : NBR_MAX;
+  __syncthreads();
+  const bool phase0 = s_phase0 != 0;  // some sphere can start or be released
+
+  const double L = (double)sel3(g, d.nx, d.ny, d.nz);
+  const int wall = sel3(g, d.walls[0], d.walls[1], d.walls[2]);
+  for (int sub = 0; sub < d.n_sub; ++sub) {
+    double *u1 = su + (sub & 1 ? 0 : 3 * P), *w1 = sw + (sub & 1 ? 0 : 3 * P);
+    const GroupState s = {sx, su + (sub & 1 ? 3 * P : 0), sw + (sub & 1 ? 3 * P : 0), sR, sm};
+    // phase 0: release below the gap, start force of newly free spheres; phase
+    // 1 (after the positions): forces and velocities.  One loop, so that the
+    // force code is there once.
+    for (int phase = phase0 ? 0 : 1; phase < 2; ++phase) {
+      bool act = on;
+      if (phase == 0) {
+        // lanes 0-2 each take one axis of gap_ahead
+        const bool near = own && g < 3 && fmin(1e300, axis_gap_ahead(x, R, ut, wall, L)) < gap;
+        if (mode == MODE_PRESCRIBED && ((__ballot(near) >> base) & 0xFFull)) {
+          mode = MODE_FREE;
+          old = 0;
+        }
+        act = on && mode == MODE_FREE && !old;
+        old = act ? 1 : old;
+      } else {
+        if (own && g < 3) {
+          x = next_position(mode, x, v, fold, cpos, dtp, L, wall);
+          sx[3 * i + g] = x;
+        }
+        __syncthreads();
+      }
+      if (__any(act)) {
+        double lub, col;
+        group_forces(d, s, i, act, nn, [&](int k) { return (int)snbr[NBR_MAX * i + k]; }, shid + HIST_SLOTS * i,
+                     shd + 3 * HIST_SLOTS * i, phase == 1, phase == 1, dtp, &lub, &col);
+        if (act && g < 6) {
+          const double F = total_term(ffp, lub, col, fext, g < 3);
+          if (phase == 1) {
+            if (mode == MODE_FREE) {
+              v = next_velocity(v, fold, F, cvel);
+            } else if (mode == MODE_PRESCRIBED) {
+              t += dtp;
+              v = g < 3 ? prescribed_velocity(ut, c_acc, t_st, t) : 0.0;
+            }
+            if (g < 3)
+              u1[3 * i + c] = v;
+            else
+              w1[3 * i + c] = v;
+            if (sub == d.n_sub - 1) {
+              p.diag[18 * i + g] = F;
+              p.diag[18 * i + 6 + g] = lub;
+              p.diag[18 * i + 12 + g] = col;
+            }
+          }
+          if (mode == MODE_FREE) fold = F;
+        }
+      }
+      __syncthreads();
+    }
+  }
+
+  if (own) {
+    if (g < 3) p.x[3 * i + g] = x;
+    (g < 3 ? p.u : p.w)[3 * i + c] = v;
+    p.Fold[6 * i + g] = fold;
+    if (!(isfinite(v) && isfinite(x))) atomicOr(d.status, ST_NONFINITE);
+    if (g == 0) {
+      p.tpresc[i] = t;
+      p.mode[i] = mode;
+      p.old_valid[i] = old;
+    }
+  }
+  for (int k = tid; k < HIST_SLOTS * P; k += T) p.hist_id[k] = shid[k];
+  for (int k = tid; k < 3 * HIST_SLOTS * P; k += T) p.hist_d[k] = shd[k];
+}
+
+// threads of the few-sphere kernel: one wavefront, whose barriers cost nothing,
+// up to eight spheres
+constexpr int DEM_LDS_THREADS = GROUP * DEM_LDS_MAX;
+static unsigned dem_lds_threads(int P) { return P <= 8 ? 64u : (P <= 32 ? 256u : (unsigned)DEM_LDS_THREADS); }
 
 // The one-workgroup kernels run beside the sweep in an overlapped step: they
 // are a chain of dependent FP64 work, so their waves take the highest issue
 // priority on the CUs they share with the sweep's waves.
-__global__ __launch_bounds__(256) void k_dem_lds(DevDomain d) {
+extern __shared__ double dem_smem[];
+
+__global__ __launch_bounds__(DEM_LDS_THREADS) void k_dem_lds(DevDomain d) {
   __builtin_amdgcn_s_setprio(3);
   if (dem_stopped(d)) return;
-  dem_lds_run(d);
+  dem_lds_run(d, (unsigned char*)dem_smem);
 }
 
 // many domains, one workgroup each (the few-sphere kernels above)
-__global__ __launch_bounds__(256) void k_dem_batch(const DevDomain* __restrict__ tab, int ndom) {
+__global__ __launch_bounds__(DEM_LDS_THREADS) void k_dem_batch(const DevDomain* __restrict__ tab, int ndom) {
   const DevDomain& d = tab[blockIdx.x];
-  if (dem_stopped(d)) return;
+  if (dem_stopped(d) || d.P <= 0) return;
   if (d.P <= DEM_LDS_MAX)
-    dem_lds_run(d);
+    dem_lds_run(d, (unsigned char*)dem_smem);
   else
     dem_global_run(d);
 }
 
 void launch_dem_batch(const BatchTables& b, hipStream_t s) {
-  if (b.ndom > 0) hipLaunchKernelGGL(k_dem_batch, dim3(b.ndom), dim3(256), 0, s, b.tab, b.ndom);
+  const int P = b.max_P < DEM_LDS_MAX ? b.max_P : DEM_LDS_MAX;
+  if (b.ndom > 0 && b.max_P > 0)
+    hipLaunchKernelGGL(k_dem_batch, dim3(b.ndom), dim3(b.max_P > DEM_LDS_MAX ? 256u : dem_lds_threads(P)),
+                       dem_lds_bytes(P), s, b.tab, b.ndom);
 }
 
 void launch_advance(const DevDomain& d, hipStream_t s) { hipLaunchKernelGGL(k_advance, dim3(1), dim3(1), 0, s, d); }
@@ -616,53 +920,55 @@ __device__ __forceinline__ void bin_insert(const DevDomain& d, const DevParticle
     atomicOr(d.status, ST_NBR_FULL);
 }
 
-// the neighbour test of dem_body over the candidates of the surrounding bins,
-// kept sorted by id, so both kernels produce the same list
-__device__ __forceinline__ void binned_neighbours(const DevDomain& d, const DevParticles& p, int i) {
-  const double* x = p.x + 3 * i;
-  if (!(isfinite(x[0]) && isfinite(x[1]) && isfinite(x[2]))) {
-    p.nbr_n[i] = 0;
-    return;
-  }
-  const double range = list_range(d);
-  int b[3];
-  bin_index(d, x, b);
-  const int n0 = d.bins.n[0], n1 = d.bins.n[1], n2 = d.bins.n[2];
-  int* out = p.nbr + (size_t)i * NBR_MAX;
-  int cnt = 0;
-  for (int ez = 0; ez < axis_count(n2); ++ez) {
-    int kz;
-    if (!axis_bin(b[2], n2, d.walls[2], ez, &kz)) continue;
-    for (int ey = 0; ey < axis_count(n1); ++ey) {
-      int ky;
-      if (!axis_bin(b[1], n1, d.walls[1], ey, &ky)) continue;
-      for (int ex = 0; ex < axis_count(n0); ++ex) {
-        int kx;
-        if (!axis_bin(b[0], n0, d.walls[0], ex, &kx)) continue;
-        const int* c = d.bins.cell + (size_t)(kx + n0 * (ky + n1 * kz)) * (1 + BIN_CAP);
-        const int m = min(c[0], BIN_CAP);
-        for (int e = 0; e < m; ++e) {
-          const int j = c[1 + e];
-          if (j == i || !(pair_gap(d, p, i, j) < range)) continue;
-          if (cnt < NBR_MAX) {
-            int pos = cnt;
-            while (pos > 0 && out[pos - 1] > j) {
-              out[pos] = out[pos - 1];
-              --pos;
-            }
-            out[pos] = j;
-          } else {
-            atomicOr(d.status, ST_NBR_FULL);
-          }
-          cnt++;
-        }
+// The neighbour test of dem_body over the candidates of the surrounding bins,
+// by 32 lanes per sphere: lane e takes the e-th of the 27 bins, so the bins'
+// counts and ids are read in two round trips instead of 27 one after the other
+// (10,000 spheres beside the 384^3 sweep: 253 -> 23 us).  The partners are collected in LDS in any order and then
+// written by rank (ids are distinct), so every kernel produces the same list.
+constexpr int NBR_LANES = 32;
+__device__ __forceinline__ void binned_neighbours(const DevDomain& d, const DevParticles& p, int i, int* cand,
+                                                  int* ncand) {
+  const int e = threadIdx.x & (NBR_LANES - 1);
+  const bool on = i < d.P;
+  if (e == 0) *ncand = 0;
+  __syncthreads();
+  const double* x = p.x + 3 * (on ? i : 0);
+  if (on && isfinite(x[0]) && isfinite(x[1]) && isfinite(x[2])) {
+    const double range = list_range(d);
+    int b[3];
+    bin_index(d, x, b);
+    const int n0 = d.bins.n[0], n1 = d.bins.n[1], n2 = d.bins.n[2];
+    const int a0 = axis_count(n0), a1 = axis_count(n1), a2 = axis_count(n2);
+    int kx, ky, kz;
+    if (e < a0 * a1 * a2 && axis_bin(b[0], n0, d.walls[0], e % a0, &kx) &&
+        axis_bin(b[1], n1, d.walls[1], e / a0 % a1, &ky) && axis_bin(b[2], n2, d.walls[2], e / (a0 * a1), &kz)) {
+      const int* c = d.bins.cell + (size_t)(kx + n0 * (ky + n1 * kz)) * (1 + BIN_CAP);
+      const int m = min(c[0], BIN_CAP);
+      for (int k = 0; k < m; ++k) {
+        const int j = c[1 + k];
+        if (j == i || !(pair_gap(d, p, i, j) < range)) continue;
+        const int at = atomicAdd(ncand, 1);
+        if (at < NBR_MAX)
+          cand[at] = j;
+        else
+          atomicOr(d.status, ST_NBR_FULL);
       }
     }
   }
-  p.nbr_n[i] = cnt < NBR_MAX ? cnt : NBR_MAX;
+  __syncthreads();
+  const int n = min(*ncand, NBR_MAX);
+  if (!on) return;
+  int* out = p.nbr + (size_t)i * NBR_MAX;
+  for (int k = e; k < n; k += NBR_LANES) {
+    const int j = cand[k];
+    int rank = 0;
+    for (int q = 0; q < n; ++q) rank += cand[q] < j;
+    out[rank] = j;
+  }
+  if (e == 0) p.nbr_n[i] = n;
 }
 
-// Many spheres: one thread per sphere, the sub-cycles as a chain of ordinary
+// Many spheres: a group of lanes per sphere, the sub-cycles as a chain of ordinary
 // launches (a kernel boundary wherever every sphere must see the others'
 // state): the momentum-exchange sums and the bins, the neighbour lists, then
 // per sub-cycle the positions (into the other buffer) and the forces and
@@ -679,10 +985,37 @@ __global__ __launch_bounds__(DEM_GRID_THREADS) void k_demg_prologue(DevDomain d)
   if (lane == 0) bin_insert(d, d.p, i);
 }
 
+// the same where each sphere has one partial (one block per sphere in the
+// boundary pass): lane g < 6 of its group takes component g
+__global__ __launch_bounds__(DEM_GRID_THREADS) void k_demg_prologue_one(DevDomain d) {
+  if (dem_stopped(d)) return;
+  const int g = threadIdx.x & (GROUP - 1);
+  const int i = (int)((blockIdx.x * blockDim.x + threadIdx.x) / GROUP);
+  if (i >= d.P) return;
+  const DevParticles& p = d.p;
+  if (g < 6) {
+    const int k = 6 * i + g;
+    const double F = 0.0 + d.partial[k];
+    p.Fraw[k] = F;
+    if (d.force_averaging) {
+      const double prev = p.prev_valid[i] ? p.Fprev[k] : F;
+      p.Ffp[k] = 0.5 * (F + prev);
+      p.Fprev[k] = F;
+    } else {
+      p.Ffp[k] = F;
+    }
+  }
+  if (g < 3) p.xmap[3 * i + g] = p.x[3 * i + g];
+  if (g == 7) bin_insert(d, p, i);
+  if (g == 0 && d.force_averaging) p.prev_valid[i] = 1;
+}
+
 __global__ __launch_bounds__(DEM_GRID_THREADS) void k_demg_neighbours(DevDomain d) {
   if (dem_stopped(d)) return;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < d.P) binned_neighbours(d, d.p, i);
+  constexpr int PER = DEM_GRID_THREADS / NBR_LANES;
+  __shared__ int cand[PER][NBR_MAX], ncand[PER];
+  const int s = threadIdx.x / NBR_LANES;
+  binned_neighbours(d, d.p, (int)blockIdx.x * PER + s, cand[s], &ncand[s]);
 }
 
 // state of sub-cycle `sub` (even: the first buffers), and the other buffer
@@ -715,31 +1048,60 @@ __global__ __launch_bounds__(DEM_GRID_THREADS) void k_demg_position(DevDomain d,
 }
 
 // forces at the new positions with the old velocities, new velocities into
-// the other buffer; after the last sub-cycle the state is copied back if it
-// ended in the second buffers (odd n_sub, a kernel of its own) and checked.
-// With `fuse` the thread then advances its own sphere's position of the next
-// sub-cycle: nothing in this launch reads the buffer that goes into, and that
-// step reads only the sphere's own state -- valid when no sphere can be
-// released from a prescribed motion (a release evaluates forces on every
-// partner's state, which needs the sub-cycle's launch boundary).
+// the other buffer, by a group of eight lanes per sphere (one thread per
+// sphere walked its partners one after the other, a chain of memory round
+// trips per partner: 10,000 spheres beside the 384^3 sweep 77 -> 41 us per
+// sub-cycle); after the last sub-cycle the state is
+// copied back if it ended in the second buffers (odd n_sub, a kernel of its
+// own) and checked.  With `fuse` the group then advances its own sphere's
+// position of the next sub-cycle: nothing in this launch reads the buffer that
+// goes into, and that step reads only the sphere's own state -- valid when no
+// sphere can be released from a prescribed motion (a release evaluates forces
+// on every partner's state, which needs the sub-cycle's launch boundary).
 __global__ __launch_bounds__(DEM_GRID_THREADS) void k_demg_velocity(DevDomain d, int sub, int fuse) {
   if (dem_stopped(d)) return;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= d.P) return;
+  const int g = threadIdx.x & (GROUP - 1);
+  const int gi = (int)((blockIdx.x * blockDim.x + threadIdx.x) / GROUP);
+  const bool on = gi < d.P;  // every lane stays for the group's shuffles
+  const int i = on ? gi : 0;
   DevParticles a;
   double *x1, *u1, *w1;
   subcycle_buffers(d.p, sub, a, &x1, &u1, &w1);
-  DevParticles b = a;
-  b.x = x1;
   const double dtp = 1.0 / (double)d.n_sub;
-  eval_forces(d, b, i, true, true, dtp, d.p.Fnew + 6 * i, d.p.Fnew + 6 * i + 3);
-  advance_velocity(d, b, i, dtp, u1 + 3 * i, w1 + 3 * i);
-  if (sub == d.n_sub - 1 && !(d.n_sub & 1)) health_check(d, d.p, i);
-  if (fuse) {
-    DevParticles n;
-    double *xn, *un, *wn;
-    subcycle_buffers(d.p, sub + 1, n, &xn, &un, &wn);
-    advance_position(d, n, i, dtp, xn + 3 * i);
+  const GroupState s = {x1, a.u, a.w, a.R, a.m};
+  const int* nbr = a.nbr + (size_t)i * NBR_MAX;
+  double lub, col;
+  group_forces(d, s, i, on, a.nbr_n[i], [&](int k) { return nbr[k]; }, a.hist_id + (size_t)i * HIST_SLOTS,
+               a.hist_d + (size_t)i * HIST_SLOTS * 3, true, true, dtp, &lub, &col);
+  if (!on || g >= 6) return;
+  const int c = g < 3 ? g : g - 3, k = 6 * i + g;
+  const double F = group_total(d, g, lub, col, a.Ffp[k], buoyant_mass(a.R[i], a.rho[i]));
+  const int mode = a.mode[i];
+  const double v0 = g < 3 ? a.u[3 * i + c] : a.w[3 * i + c];
+  double v1 = v0, fold = 0.0;
+  if (mode == MODE_FREE) {
+    fold = F;
+    v1 = next_velocity(v0, a.Fold[k], F, velocity_factor(g < 3 ? a.m[i] : a.I[i], dtp));
+    a.Fold[k] = F;
+  } else if (mode == MODE_PRESCRIBED) {
+    const double t = a.tpresc[i] + dtp;
+    v1 = g < 3 ? prescribed_velocity(a.presc[6 * i + c], a.presc[6 * i + 3], a.presc[6 * i + 4], t) : 0.0;
+    if (g == 0) a.tpresc[i] = t;
+  }
+  (g < 3 ? u1 : w1)[3 * i + c] = v1;
+  const bool last = sub == d.n_sub - 1;
+  if (last) {
+    a.diag[18 * i + g] = F;
+    a.diag[18 * i + 6 + g] = lub;
+    a.diag[18 * i + 12 + g] = col;
+    if (!(d.n_sub & 1) && !(isfinite(v1) && (g >= 3 || isfinite(x1[3 * i + c])))) atomicOr(d.status, ST_NONFINITE);
+  }
+  if (fuse && g < 3) {
+    // position of the next sub-cycle, into the buffer x came from
+    double* xn = sub & 1 ? d.p.x2 : d.p.x;
+    const int n = sel3(g, d.nx, d.ny, d.nz);
+    xn[3 * i + g] = next_position(mode, x1[3 * i + g], v1, fold, position_factor(a.m[i], dtp), dtp, (double)n,
+                                 sel3(g, d.walls[0], d.walls[1], d.walls[2]));
   }
 }
 
@@ -756,31 +1118,34 @@ __global__ __launch_bounds__(DEM_GRID_THREADS) void k_demg_epilogue(DevDomain d)
   health_check(d, p, i);
 }
 
-bool dem_many(const DevDomain& d, int kernel) { return kernel == 2 || (kernel == 0 && d.P > DEM_GRID_MIN); }
+bool dem_many(const DevDomain& d, int kernel) { return kernel == 2 || (kernel == 0 && d.P > DEM_LDS_MAX); }
 
 hipError_t launch_dem(const DevDomain& d, int kernel, bool no_release, hipStream_t s) {
   if (d.P <= 0) return hipSuccess;
   if (!dem_many(d, kernel)) {
-    // up to 64 spheres one wavefront (its barriers cost nothing; 1 sphere
-    // beside an FP64 sweep: 250 against 260 us), else four
-    const unsigned T1 = d.P <= 64 ? 64u : 256u;
     if (d.P <= DEM_LDS_MAX)
-      hipLaunchKernelGGL(k_dem_lds, dim3(1), dim3(T1), 0, s, d);
+      hipLaunchKernelGGL(k_dem_lds, dim3(1), dim3(dem_lds_threads(d.P)), dem_lds_bytes(d.P), s, d);
     else
-      hipLaunchKernelGGL(k_dem, dim3(1), dim3(T1), 0, s, d);
+      hipLaunchKernelGGL(k_dem, dim3(1), dim3(256), 0, s, d);
     return hipGetLastError();
   }
   const unsigned T = DEM_GRID_THREADS;
-  const unsigned blocks = (unsigned)((d.P + T - 1) / T);
-  hipLaunchKernelGGL(k_demg_prologue, dim3((unsigned)(((long long)d.P * 64 + T - 1) / T)), dim3(T), 0, s, d);
-  hipLaunchKernelGGL(k_demg_neighbours, dim3(blocks), dim3(T), 0, s, d);
-  hipLaunchKernelGGL(k_demg_position, dim3(blocks), dim3(T), 0, s, d, 0);
+  auto grid = [&](int lanes) { return dim3((unsigned)(((long long)d.P * lanes + T - 1) / T)); };
+  if (d.ZB * d.RB == 1)
+    hipLaunchKernelGGL(k_demg_prologue_one, grid(GROUP), dim3(T), 0, s, d);
+  else
+    hipLaunchKernelGGL(k_demg_prologue, grid(64), dim3(T), 0, s, d);
+  hipLaunchKernelGGL(k_demg_neighbours, grid(NBR_LANES), dim3(T), 0, s, d);
+  // (its threads also clear the bins, a few each: with only the threads of 156
+  // spheres that alone took 20 us)
+  const long long clear = ((long long)d.bins.n[0] * d.bins.n[1] * d.bins.n[2] + 4 * T - 1) / (4 * T);
+  hipLaunchKernelGGL(k_demg_position, dim3(std::max(grid(1).x, (unsigned)clear)), dim3(T), 0, s, d, 0);
   for (int sub = 0; sub < d.n_sub; ++sub) {
     const int fuse = no_release && sub + 1 < d.n_sub ? 1 : 0;
-    hipLaunchKernelGGL(k_demg_velocity, dim3(blocks), dim3(T), 0, s, d, sub, fuse);
-    if (!fuse && sub + 1 < d.n_sub) hipLaunchKernelGGL(k_demg_position, dim3(blocks), dim3(T), 0, s, d, sub + 1);
+    hipLaunchKernelGGL(k_demg_velocity, grid(GROUP), dim3(T), 0, s, d, sub, fuse);
+    if (!fuse && sub + 1 < d.n_sub) hipLaunchKernelGGL(k_demg_position, grid(1), dim3(T), 0, s, d, sub + 1);
   }
-  if (d.n_sub & 1) hipLaunchKernelGGL(k_demg_epilogue, dim3(blocks), dim3(T), 0, s, d);
+  if (d.n_sub & 1) hipLaunchKernelGGL(k_demg_epilogue, grid(1), dim3(T), 0, s, d);
   return hipGetLastError();
 }
 

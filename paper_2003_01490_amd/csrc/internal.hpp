@@ -249,6 +249,7 @@ struct BatchTables {
   const int* claim_start;   // P * ZB blocks per domain (claims, reconstruction)
   const int* commit_start;  // P * ZB * RB sphere blocks per domain
   int ndom;
+  int max_P;  // most spheres in one domain
   int sweep_blocks, claim_blocks, commit_blocks;
   int storage;
 };
@@ -356,8 +357,12 @@ hipError_t launch_dem(const DevDomain& d, int kernel, bool no_release, hipStream
 // whether launch_dem takes the many-sphere chain
 bool dem_many(const DevDomain& d, int kernel);
 constexpr int DEM_GRID_THREADS = 128;
-// automatic DEM kernel choice: above this many spheres the many-sphere chain
-constexpr int DEM_GRID_MIN = 256;
+// Spheres of the one-workgroup DEM kernel (eight lanes each, state in LDS and
+// registers); automatic choice: above this many the many-sphere chain.  A
+// larger workgroup would have to take the spheres in rounds: 156 spheres took
+// 161 us in three rounds of 512 threads, the chain 107 us; 40 spheres 78 us
+// against about 100.
+constexpr int DEM_LDS_MAX = 64;
 void launch_fields(const DevDomain& d, int field, double* dst, hipStream_t s);
 void launch_set_pdf(const DevDomain& d, int q, const double* src, hipStream_t s);
 // densities at n points: io holds 3n coordinates, then receives n results

@@ -1,0 +1,74 @@
+"""DEM kernels with a group of eight lanes per sphere: the sphere counts where
+the workgroup's shape, the LDS layout or the choice of kernel changes (one
+wavefront up to 8 spheres, 256 threads up to 32, 512 up to 64, global memory
+beyond), in a box crowded enough for contacts and lubrication between many
+partners of one sphere (more than the eight lanes take at once, for the large
+counts in the small box)."""
+import numpy as np
+import pytest
+
+from paper_2003_01490_amd import workloads as W
+
+from harness import check_all, fp64_bounds, gpu_domain, oracle_domain, sphere_errs
+
+pytestmark = pytest.mark.gpu
+
+# FP64 rounding of a sum of ~1,000 links of size 2 w_q relative to the largest
+# force of the run is ~2e-13; 15 steps and the lubrication's gain leave an
+# order of magnitude each way below this
+BOUND = 1e-11
+
+
+@pytest.mark.parametrize("count", [1, 7, 8, 9, 32, 33, 64, 65])
+def test_lane_groups_against_oracle(count):
+    D, n = 6.0, 24 if count <= 9 else (32 if count <= 33 else 40)
+    wl = W.dense(count, n=n, count=count, D=D, min_gap=0.05, u_rms=0.08, nu=0.02)
+    print(f"[case] {count} spheres D=6 in {n}^3, FP64, 15 steps", flush=True)
+    o = oracle_domain(wl)
+    gs = [gpu_domain(wl, dem_kernel=1, map_kernel=1), gpu_domain(wl, dem_kernel=2, map_kernel=1)]
+    u = float(np.abs(wl.u).max())
+    o.step(15)
+    so = [o.sphere(i) for i in range(count)]
+    F = max(max(float(np.abs(s["F_tot"]).max()), float(np.abs(s["F_fp"]).max())) for s in so)
+    for g in gs:
+        g.step(15)
+        g.sync()
+        for i in range(count):
+            check_all(sphere_errs(g.sphere(i), so[i], D, {"u": u, "F": F}),
+                      fp64_bounds(**{k: BOUND for k in ("x", "u", "w", "F_fp", "F_raw", "F_tot", "F_lub", "F_col",
+                                                        "T_fp", "T_raw")}), f"sphere {i}")
+    a, b = gs[0].spheres(), gs[1].spheres()
+    assert all(np.array_equal(a[k], b[k]) for k in a), "the two kernels differ"
+
+
+@pytest.mark.parametrize("lub_mask", [0, 7])
+def test_many_partners_of_one_sphere(lub_mask):
+    """A large sphere with 20 small ones around it (three rounds of the eight
+    lanes), all in contact without lubrication (more than eight histories) or
+    all in lubrication range, both kernels against the oracle."""
+    R, r = 8.0, 1.5
+    c = np.array([20.3, 19.8, 20.1])
+    k = np.arange(20) + 0.5
+    th, ph = np.arccos(1 - 2 * k / 20), np.pi * (1 + 5 ** 0.5) * k
+    dirs = np.stack([np.cos(ph) * np.sin(th), np.sin(ph) * np.sin(th), np.cos(th)], 1)
+    x = np.concatenate([c[None], c + dirs * (R + r + 0.02)])
+    u = np.concatenate([np.zeros((1, 3)), -0.03 * dirs])
+    p = W.base_params(nx=40, ny=40, nz=40, nu=0.05, tc=8.0, max_spheres=21, lub_mask=lub_mask)
+    wl = W.Workload("partners", p, x, np.array([R] + [r] * 20), np.full(21, 3.0), u, np.zeros((21, 3)), 8)
+    print("[case] one sphere R=8 with 20 of R=1.5 around it, FP64, 8 steps", flush=True)
+    o = oracle_domain(wl)
+    o.step(8)
+    so = [o.sphere(i) for i in range(21)]
+    near = sum(bool(np.abs(s["F_lub" if lub_mask else "F_col"]).max() > 0) for s in so[1:])
+    assert near > 8, f"only {near} partners in reach"
+    F = max(max(float(np.abs(s["F_tot"]).max()), float(np.abs(s["F_fp"]).max())) for s in so)
+    gs = [gpu_domain(wl, dem_kernel=1), gpu_domain(wl, dem_kernel=2)]
+    for g in gs:
+        g.step(8)
+        g.sync()
+        for i in range(21):
+            check_all(sphere_errs(g.sphere(i), so[i], 2 * wl.R[i], {"u": 0.03, "F": F}),
+                      fp64_bounds(**{k: BOUND for k in ("x", "u", "w", "F_fp", "F_raw", "F_tot", "F_lub", "F_col",
+                                                        "T_fp", "T_raw")}), f"sphere {i}")
+    a, b = gs[0].spheres(), gs[1].spheres()
+    assert all(np.array_equal(a[k], b[k]) for k in a), "the two kernels differ"
