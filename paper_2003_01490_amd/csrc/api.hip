@@ -547,6 +547,7 @@ int32_t lbmdem_create(const lbmdem_config* cfg, void* dev_buf, size_t dev_bytes,
     default: d.s_minus = snu; d.s_bulk_shell = snu; d.s_bulk_other = snu; break;
   }
   d.delta_ab = cfg->delta_ab;
+  sweep_tiles(d.nx, d.ny, d.storage, 256, &d.sw_bx, &d.sw_by, &d.sw_gx, &d.sw_gy);
   d.pdf[0] = base + L.pdf0;
   d.pdf[1] = base + L.pdf1;
   d.flags = (uint8_t*)(base + L.flags);
@@ -1175,13 +1176,13 @@ bool same_config(const lbmdem_config& a, const lbmdem_config& b) {
   return eq;
 }
 
-// device segments of a checkpoint: the current PDF buffer, the cell arrays
-// (flags, owners and, where the domain has them, claims, shell stamps and
-// cell words) and the particle block
-void ck_segments(const lbmdem_domain* dom, int cur, char** at, size_t* len) {
+// device segments of a checkpoint: the current PDF buffer (written plane by
+// plane, see below), the cell arrays (flags, owners and, where the domain has
+// them, claims, shell stamps and cell words) and the particle block
+void ck_segments(const lbmdem_domain* dom, char** at, size_t* len) {
   char* base = (char*)dom->region;
   const Layout& L = dom->L;
-  at[0] = base + (cur ? L.pdf1 : L.pdf0);
+  at[0] = nullptr;
   len[0] = L.pdf1 - L.pdf0;
   at[1] = base + L.flags;
   len[1] = L.stage - L.flags;
@@ -1190,6 +1191,24 @@ void ck_segments(const lbmdem_domain* dom, int cur, char** at, size_t* len) {
 }
 
 }  // namespace
+
+// The populations lie in a checkpoint as 19 planes of N stored values, zero
+// padded to the segment's length: a format of its own, whatever the layout in
+// the region, so that a checkpoint outlives a change of that layout.
+static int32_t ck_pdf(lbmdem_domain* dom, int cur, char* blob, size_t len, bool save) {
+  const size_t plane = (size_t)dom->d.N * storage_size(dom->cfg.storage);
+  char* stage = (char*)dom->region + dom->L.stage;
+  hipStream_t st = dom->stream;
+  for (int q = 0; q < Q; ++q) {
+    char* at = blob + plane * (size_t)q;
+    if (!save) HIPCHK(dom, hipMemcpyAsync(stage, at, plane, hipMemcpyHostToDevice, st));
+    launch_plane_copy(dom->d, cur, q, stage, save, st);
+    HIPCHK(dom, hipGetLastError());
+    if (save) HIPCHK(dom, hipMemcpyAsync(at, stage, plane, hipMemcpyDeviceToHost, st));
+  }
+  if (save) std::memset(blob + plane * Q, 0, len - plane * Q);
+  return LBMDEM_OK;
+}
 
 static int32_t read_ctl(lbmdem_domain* dom, DevCtl* c) {
   HIPCHK(dom, hipMemcpyAsync(c, dom->d.ctl, sizeof(DevCtl), hipMemcpyDeviceToHost, dom->stream));
@@ -1203,7 +1222,7 @@ int32_t lbmdem_save(lbmdem_domain* dom, void* host_blob, size_t* bytes) {
   if (int32_t rc = read_ctl(dom, &c)) return rc;
   char* at[3];
   size_t len[3];
-  ck_segments(dom, c.cur, at, len);
+  ck_segments(dom, at, len);
   const size_t P = dom->hR.size();
   const size_t need = sizeof(CkHeader) + 8 * P + len[0] + len[1] + len[2];
   if (!host_blob) {
@@ -1228,7 +1247,9 @@ int32_t lbmdem_save(lbmdem_domain* dom, void* host_blob, size_t* bytes) {
   out += sizeof(h);
   if (P) std::memcpy(out, dom->hR.data(), 8 * P);
   out += 8 * P;
-  for (int k = 0; k < 3; ++k) {
+  if (int32_t rc = ck_pdf(dom, c.cur, out, len[0], true)) return rc;
+  out += len[0];
+  for (int k = 1; k < 3; ++k) {
     HIPCHK(dom, hipMemcpyAsync(out, at[k], len[k], hipMemcpyDeviceToHost, dom->stream));
     out += len[k];
   }
@@ -1251,7 +1272,7 @@ int32_t lbmdem_restore(lbmdem_domain* dom, const void* host_blob, size_t bytes) 
   harvest(dom);
   char* at[3];
   size_t len[3];
-  ck_segments(dom, h.cur, at, len);
+  ck_segments(dom, at, len);
   const size_t need = sizeof(CkHeader) + 8 * (size_t)h.P + len[0] + len[1] + len[2];
   if (bytes < need || h.seg[0] != len[0] || h.seg[1] != len[1] || h.seg[2] != len[2])
     return fail(dom, LBMDEM_EINVAL, "checkpoint size does not match this domain");
@@ -1260,7 +1281,9 @@ int32_t lbmdem_restore(lbmdem_domain* dom, const void* host_blob, size_t bytes) 
   in += 8 * (size_t)h.P;
   // the step state (current buffer, stamp, step count) is part of the
   // particle block
-  for (int k = 0; k < 3; ++k) {
+  if (int32_t rc = ck_pdf(dom, h.cur, const_cast<char*>(in), len[0], false)) return rc;
+  in += len[0];
+  for (int k = 1; k < 3; ++k) {
     HIPCHK(dom, hipMemcpyAsync(at[k], in, len[k], hipMemcpyHostToDevice, dom->stream));
     in += len[k];
   }
@@ -1403,7 +1426,7 @@ static int32_t build_tables(lbmdem_batch* b) {
     dom->d.P = P[k];
     tab[k] = dom->d;
     const DevDomain& d = dom->d;
-    ss[k + 1] = ss[k] + (int)((d.N + 255) / 256);
+    ss[k + 1] = ss[k] + d.sw_gx * d.sw_gy * d.nz;
     cs[k + 1] = cs[k] + d.P * d.ZB;
     ms[k + 1] = ms[k] + d.P * d.ZB * d.RB;
   }

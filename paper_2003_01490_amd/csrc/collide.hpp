@@ -16,7 +16,8 @@ struct Store<double> {
   using C = double;
   __device__ static inline double load(const double* p) { return *p; }
   __device__ static inline double load_nt(const double* p) { return __builtin_nontemporal_load(p); }
-  __device__ static inline void store(double* p, double v) { __builtin_nontemporal_store(v, p); }
+  __device__ static inline void store(double* p, double v) { *p = v; }
+  __device__ static inline void store_nt(double* p, double v) { __builtin_nontemporal_store(v, p); }
 };
 
 template <>
@@ -24,7 +25,8 @@ struct Store<float> {
   using C = float;
   __device__ static inline float load(const float* p) { return *p; }
   __device__ static inline float load_nt(const float* p) { return __builtin_nontemporal_load(p); }
-  __device__ static inline void store(float* p, float v) { __builtin_nontemporal_store(v, p); }
+  __device__ static inline void store(float* p, float v) { *p = v; }
+  __device__ static inline void store_nt(float* p, float v) { __builtin_nontemporal_store(v, p); }
 };
 
 template <>
@@ -35,7 +37,8 @@ struct Store<__half> {
     const unsigned short b = __builtin_nontemporal_load(reinterpret_cast<const unsigned short*>(p));
     return __half2float(*reinterpret_cast<const __half*>(&b));
   }
-  __device__ static inline void store(__half* p, float v) {
+  __device__ static inline void store(__half* p, float v) { *p = __float2half_rn(v); }
+  __device__ static inline void store_nt(__half* p, float v) {
     __half h = __float2half_rn(v);
     __builtin_nontemporal_store(*reinterpret_cast<unsigned short*>(&h),
                                 reinterpret_cast<unsigned short*>(p));
@@ -46,7 +49,7 @@ struct Store<__half> {
 // qb): the value pulled from the wall cell x - c_q becomes
 // f~_qb(x) + 6 w (u_w . c_q); in deviations the weights cancel.
 #define WALL_BB(q, qb, w, cx, cy, cz, ux, uy, uz)                                         \
-  g[q] = (C)((double)Store<T>::load(src + (size_t)(qb) * NN + idx) +                       \
+  g[q] = (C)((double)Store<T>::load(own + (size_t)(qb) * (size_t)nx) +                      \
              6.0 * (w) * ((ux) * (cx) + (uy) * (cy) + (uz) * (cz)))
 
 // The five directions whose source lies across one wall layer, per side.  The
@@ -85,28 +88,25 @@ struct Store<__half> {
 // 0), which adds -3/2 (s_b - s+) u.a to that row's correction.  On the
 // conserved momentum TRT's odd rate and the moment-space rate 0 give the same
 // j + a.
-// Pull of the 19 values of cell (x, y, z) (index idx) from the source buffer,
+// Pull of the 19 values of cell (x, y, z) from the source buffer,
 // with the values that come from a wall layer replaced by the moving-wall
 // bounce-back of Sec. 2.2.
 template <typename T, bool NTLOAD = false>
 __device__ __forceinline__ void pull_cell(const DevDomain& d, const T* __restrict__ src, int x, int y, int z,
-                                          unsigned int idx, typename Store<T>::C* g) {
+                                          typename Store<T>::C* g) {
   using C = typename Store<T>::C;
   const int nx = d.nx, ny = d.ny, nz = d.nz;
-  const unsigned int nxy = (unsigned int)nx * (unsigned int)ny;
 
-  // source of direction q is x - c_q: index [1 - c] of these triples
-  const unsigned int X0 = (unsigned int)(x == 0 ? nx - 1 : x - 1), X1 = (unsigned int)x,
-                     X2 = (unsigned int)(x == nx - 1 ? 0 : x + 1);
-  const unsigned int Y0 = (unsigned int)(y == 0 ? ny - 1 : y - 1) * (unsigned int)nx,
-                     Y1 = (unsigned int)y * (unsigned int)nx,
-                     Y2 = (unsigned int)(y == ny - 1 ? 0 : y + 1) * (unsigned int)nx;
-  const unsigned int Z0 = (unsigned int)(z == 0 ? nz - 1 : z - 1) * nxy, Z1 = (unsigned int)z * nxy,
-                     Z2 = (unsigned int)(z == nz - 1 ? 0 : z + 1) * nxy;
+  // source of direction q is x - c_q: index [1 - c] of these triples; Y and Z
+  // are the row offsets of the layout (prow)
+  const size_t X0 = (size_t)(x == 0 ? nx - 1 : x - 1), X1 = (size_t)x, X2 = (size_t)(x == nx - 1 ? 0 : x + 1);
+  const size_t Y0 = prow(d, y == 0 ? ny - 1 : y - 1, 0), Y1 = prow(d, y, 0), Y2 = prow(d, y == ny - 1 ? 0 : y + 1, 0);
+  const size_t Z0 = prow(d, 0, z == 0 ? nz - 1 : z - 1), Z1 = prow(d, 0, z), Z2 = prow(d, 0, z == nz - 1 ? 0 : z + 1);
+  const T* own = src + (Y1 + Z1 + X1);
 
-  const size_t NN = (size_t)d.N;
-#define LD(q, xs, ys, zs) \
-  (NTLOAD ? Store<T>::load_nt(src + (size_t)(q) * NN + (xs + ys + zs)) : Store<T>::load(src + (size_t)(q) * NN + (xs + ys + zs)))
+#define LD(q, xs, ys, zs)                                                       \
+  (NTLOAD ? Store<T>::load_nt(src + ((ys) + (zs) + ((size_t)(q) * (size_t)nx + (xs)))) \
+          : Store<T>::load(src + ((ys) + (zs) + ((size_t)(q) * (size_t)nx + (xs)))))
   g[0] = LD(0, X1, Y1, Z1);
   g[1] = LD(1, X1, Y0, Z1);    // c = ( 0, 1, 0)
   g[2] = LD(2, X1, Y2, Z1);    // c = ( 0,-1, 0)
@@ -147,14 +147,13 @@ __device__ __forceinline__ void pull_cell(const DevDomain& d, const T* __restric
 }
 
 // TRT+aB collision of the pulled values g (deviations) of the cell with flag
-// byte fl and storage of the results into slot idx of dst.
-template <typename T, bool FORCED>
-__device__ __forceinline__ void collide_store(const DevDomain& d, T* __restrict__ dst, unsigned int idx, uint8_t fl,
+// byte fl and storage of the results from `out` on (its direction 0 slot).
+template <typename T, bool FORCED, bool NTSTORE = true>
+__device__ __forceinline__ void collide_store(const DevDomain& d, T* __restrict__ out, uint8_t fl,
                                               typename Store<T>::C* g, typename Store<T>::C sp,
                                               typename Store<T>::C sm, typename Store<T>::C db_shell,
                                               typename Store<T>::C db_other) {
   using C = typename Store<T>::C;
-  const size_t NN = (size_t)d.N;
   // moments (rho0 = 1: u = j; deviations carry no mass or momentum of w_q)
   const C sumd = ((g[7] + g[8]) + (g[9] + g[10])) + ((g[11] + g[12]) + (g[13] + g[14])) +
                  ((g[15] + g[16]) + (g[17] + g[18]));
@@ -239,10 +238,16 @@ __device__ __forceinline__ void collide_store(const DevDomain& d, T* __restrict_
   }
 
 #pragma unroll
-  for (int q = 0; q < Q; ++q) Store<T>::store(dst + (size_t)q * NN + idx, o[q]);
+  for (int q = 0; q < Q; ++q) {
+    T* at = out + (size_t)q * (size_t)d.nx;
+    if (NTSTORE)
+      Store<T>::store_nt(at, o[q]);
+    else
+      Store<T>::store(at, o[q]);
+  }
 }
 
-template <typename T, bool FORCED, bool NTLOAD = false>
+template <typename T, bool FORCED, bool NTLOAD = false, bool NTSTORE = true>
 __device__ __forceinline__ void sweep_cell(const DevDomain& d, const T* __restrict__ src, T* __restrict__ dst,
                                            int x, int y, int z, typename Store<T>::C sp,
                                            typename Store<T>::C sm, typename Store<T>::C db_shell,
@@ -252,8 +257,8 @@ __device__ __forceinline__ void sweep_cell(const DevDomain& d, const T* __restri
                            (unsigned int)d.nx * (unsigned int)d.ny * (unsigned int)z;
   const uint8_t fl = d.flags[idx];
   C g[Q];
-  pull_cell<T, NTLOAD>(d, src, x, y, z, idx, g);
-  collide_store<T, FORCED>(d, dst, idx, fl, g, sp, sm, db_shell, db_other);
+  pull_cell<T, NTLOAD>(d, src, x, y, z, g);
+  collide_store<T, FORCED, NTSTORE>(d, dst + pidx(d, x, y, z), fl, g, sp, sm, db_shell, db_other);
 }
 #undef WALL_BB
 #undef WALLS_XP

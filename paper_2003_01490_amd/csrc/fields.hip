@@ -24,9 +24,10 @@ __global__ void k_init(DevDomain d) {
       d.shellstamp[c] = 0u;
     }
     if (d.cellw) d.cellw[c] = wall ? F_WALL : 0u;
+    const size_t p = pidx(d, i, j, k);
     for (int q = 0; q < Q; ++q) {
-      a[(size_t)q * N + c] = T(0.0f);
-      b[(size_t)q * N + c] = T(0.0f);
+      a[(size_t)q * d.nx + p] = T(0.0f);
+      b[(size_t)q * d.nx + p] = T(0.0f);
     }
   }
 }
@@ -51,6 +52,7 @@ __global__ void k_get_plane(DevDomain d, int which, double* dst) {
   for (size_t c = (size_t)blockIdx.x * blockDim.x + threadIdx.x; c < N;
        c += (size_t)gridDim.x * blockDim.x) {
     const uint8_t fl = d.flags[c];
+    const size_t p = pidx_of(d, c);
     const bool fluid = !(fl & (F_SOLID | F_WALL));
     double v = 0.0;
     if (which == 40) {
@@ -59,15 +61,15 @@ __global__ void k_get_plane(DevDomain d, int which, double* dst) {
       v = (fl & F_SOLID) ? (double)d.owner[c] : -1.0;
     } else if (which >= 60) {
       const int q = which - 60;
-      v = to_d<T>(f[(size_t)q * N + c]) + WQ[q];
+      v = to_d<T>(f[(size_t)q * d.nx + p]) + WQ[q];
     } else if (fluid) {
       if (which >= 10) {
         const int q = which - 10;
-        v = to_d<T>(f[(size_t)q * N + c]) + WQ[q];
+        v = to_d<T>(f[(size_t)q * d.nx + p]) + WQ[q];
       } else {
         double s = 0.0;
         for (int q = 0; q < Q; ++q) {
-          const double g = to_d<T>(f[(size_t)q * N + c]);
+          const double g = to_d<T>(f[(size_t)q * d.nx + p]);
           const int cq = which == 0 ? 1 : (which == 1 ? CX[q] : (which == 2 ? CY[q] : CZ[q]));
           s += g * cq;
         }
@@ -97,7 +99,22 @@ __global__ void k_set_plane(DevDomain d, int q, const double* src) {
   T* f = (T*)d.pdf[cur];
   for (size_t c = (size_t)blockIdx.x * blockDim.x + threadIdx.x; c < N;
        c += (size_t)gridDim.x * blockDim.x)
-    f[(size_t)q * N + c] = from_d<T>(src[c] - WQ[q]);
+    f[(size_t)q * d.nx + pidx_of(d, c)] = from_d<T>(src[c] - WQ[q]);
+}
+
+// one direction of a PDF buffer as a plain plane of N cells, as stored (out:
+// from the buffer into the plane, else back), for checkpoints
+template <typename T>
+__global__ void k_plane_copy(DevDomain d, int buf, int q, T* plane, int out) {
+  T* f = (T*)d.pdf[buf];
+  for (size_t c = (size_t)blockIdx.x * blockDim.x + threadIdx.x; c < (size_t)d.N;
+       c += (size_t)gridDim.x * blockDim.x) {
+    const size_t p = (size_t)q * d.nx + pidx_of(d, c);
+    if (out)
+      plane[c] = f[p];
+    else
+      f[p] = plane[c];
+  }
 }
 
 __global__ void k_copy16(uint4* __restrict__ dst, const uint4* __restrict__ src, size_t n16) {
@@ -146,10 +163,10 @@ __global__ void k_probe_density(DevDomain d, double* io, int n) {
         ijk[a] = d.walls[a] ? i0[a] + o : wrapmod(i0[a] + o, nn[a]);
         w *= o ? t[a] : 1.0 - t[a];
       }
-      const size_t cc = (size_t)cidx(d, ijk[0], ijk[1], ijk[2]);
+      const size_t cc = (size_t)cidx(d, ijk[0], ijk[1], ijk[2]), pc = pidx(d, ijk[0], ijk[1], ijk[2]);
       if (d.flags[cc] & (F_SOLID | F_WALL)) ok = false;
       double rho = 1.0;
-      for (int q = 0; q < Q; ++q) rho += to_d<T>(f[(size_t)q * N + cc]);
+      for (int q = 0; q < Q; ++q) rho += to_d<T>(f[(size_t)q * d.nx + pc]);
       r += w * rho;
     }
   }
@@ -179,8 +196,9 @@ __global__ void k_density_check(DevDomain d, int n) {
   const size_t c = n == (int)N ? (size_t)k : (size_t)(((unsigned long long)k * 2654435761ull) % N);
   if (d.flags[c] & (F_SOLID | F_WALL)) return;
   const T* f = (const T*)(d.ctl->cur ? d.pdf[1] : d.pdf[0]);
+  const size_t p = pidx_of(d, c);
   double rho = 1.0;
-  for (int q = 0; q < Q; ++q) rho += to_d<T>(f[(size_t)q * N + c]);
+  for (int q = 0; q < Q; ++q) rho += to_d<T>(f[(size_t)q * d.nx + p]);
   if (!(rho > 0.5 && rho < 1.5)) atomicOr(d.status, ST_DENSITY);
 }
 
@@ -228,6 +246,15 @@ void launch_set_pdf(const DevDomain& d, int q, const double* src, hipStream_t s)
     hipLaunchKernelGGL(k_set_plane<float>, grid_for(d.N), dim3(256), 0, s, d, q, src);
   else
     hipLaunchKernelGGL(k_set_plane<__half>, grid_for(d.N), dim3(256), 0, s, d, q, src);
+}
+
+void launch_plane_copy(const DevDomain& d, int buf, int q, void* plane, bool out, hipStream_t s) {
+  if (d.storage == 0)
+    hipLaunchKernelGGL(k_plane_copy<double>, grid_for(d.N), dim3(256), 0, s, d, buf, q, (double*)plane, out ? 1 : 0);
+  else if (d.storage == 1)
+    hipLaunchKernelGGL(k_plane_copy<float>, grid_for(d.N), dim3(256), 0, s, d, buf, q, (float*)plane, out ? 1 : 0);
+  else
+    hipLaunchKernelGGL(k_plane_copy<__half>, grid_for(d.N), dim3(256), 0, s, d, buf, q, (__half*)plane, out ? 1 : 0);
 }
 
 void launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s) {

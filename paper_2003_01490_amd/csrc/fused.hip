@@ -171,12 +171,10 @@ __global__ __launch_bounds__(FT_THREADS) __attribute__((amdgpu_waves_per_eu(4, 8
   const uint32_t stamp = d.ctl->stamp;
   const T* src = (const T*)(cur ? d.pdf[1] : d.pdf[0]);
   T* dst = (T*)(cur ? d.pdf[0] : d.pdf[1]);
-  const size_t N = (size_t)d.N;
-  const unsigned int idx = in ? (unsigned int)cidx(d, x, y, z) : 0u;
 
   // the cell's own pulls (walls replaced), in flight while the links are formed
   C g[Q];
-  if (in) pull_cell<T, false>(d, src, x, y, z, idx, g);
+  if (in) pull_cell<T, false>(d, src, x, y, z, g);
 
   for (int h = tid; h < FT_HASH; h += nthr) hkey[h] = -1;
   for (int k = tid; k < FT_TABLE * 6; k += nthr) {
@@ -336,17 +334,17 @@ __global__ __launch_bounds__(FT_THREADS) __attribute__((amdgpu_waves_per_eu(4, 8
         if (!missing) {
           const double R = tab[s][3];
           const double up[3] = {tab[s][4], tab[s][5], tab[s][6]}, wp[3] = {tab[s][7], tab[s][8], tab[s][9]};
-          const size_t cc = (size_t)cidx(d, cxx, cyy, z);
+          const size_t cc = pidx(d, cxx, cyy, z);
           const int qb = opp_of(q);
           const bool cli = d.boundary == 0 && !(swd[hcc - offq] & (F_SOLID | F_WALL));
-          const T gq = src[(size_t)q * N + cc];
-          const T gqb = src[(size_t)qb * N + cc];
+          const T gq = src[(size_t)q * d.nx + cc];
+          const T gqb = src[(size_t)qb * d.nx + cc];
           T gm = (T)0.0f;
           if (cli) {
             // x - c_q is fluid, so it is no wall cell and lies in range
             const size_t cm =
-                (size_t)cidx(d, wrapi(cxx - c[0], d.nx), wrapi(cyy - c[1], d.ny), wrapi(z - c[2], d.nz));
-            gm = src[(size_t)q * N + cm];
+                pidx(d, wrapi(cxx - c[0], d.nx), wrapi(cyy - c[1], d.ny), wrapi(z - c[2], d.nz));
+            gm = src[(size_t)q * d.nx + cm];
           }
           double r[3];
           r[0] = min_image(((double)cxx + 0.5) - xp[0], d.nx, d.walls[0]);
@@ -431,7 +429,7 @@ __global__ __launch_bounds__(FT_THREADS) __attribute__((amdgpu_waves_per_eu(4, 8
 
   // 5. collide and store (every cell, so that wavefronts write whole lines)
   if (in)
-    collide_store<T, FORCED>(d, dst, idx, (uint8_t)(wc & 0xFFu), g, (C)d.s_plus, (C)d.s_minus,
+    collide_store<T, FORCED>(d, dst + pidx(d, x, y, z), (uint8_t)(wc & 0xFFu), g, (C)d.s_plus, (C)d.s_minus,
                              (C)(d.s_bulk_shell - d.s_plus), (C)(d.s_bulk_other - d.s_plus));
 }
 

@@ -283,8 +283,7 @@ __global__ void k_new_stamp(DevCtl* ctl) { ctl->stamp += 1; }
 // fluid before and after the mapping update)
 template <typename T, typename V>
 __device__ void reconstruct_with(const DevDomain& d, T* buf, int ii, int jj, int kk, int i, V usable) {
-  const size_t N = (size_t)d.N;
-  const long long c = cidx(d, ii, jj, kk);
+  const size_t qs = (size_t)d.nx;
   double rsum = 0.0;
   int nvalid = 0;
   for (int q = 1; q < Q; ++q) {
@@ -292,7 +291,8 @@ __device__ void reconstruct_with(const DevDomain& d, T* buf, int ii, int jj, int
     const long long y = cidx(d, yi, yj, yk);
     if (!usable(y, yi, yj, yk)) continue;
     double r = 0.0;
-    for (int p = 0; p < Q; ++p) r += ldv<T>(buf + (size_t)p * N + y) + WQ[p];
+    const size_t py = pidx(d, yi, yj, yk);
+    for (int p = 0; p < Q; ++p) r += ldv<T>(buf + (size_t)p * qs + py) + WQ[p];
     rsum += r;
     nvalid += 1;
   }
@@ -319,9 +319,10 @@ __device__ void reconstruct_with(const DevDomain& d, T* buf, int ii, int jj, int
     const bool vp = usable(yp, pi, pj, pk);
     const bool vm = usable(ym, mi, mj, mk);
     double up[3] = {0, 0, 0}, um[3] = {0, 0, 0};
+    const size_t pp = pidx(d, pi, pj, pk), pm = pidx(d, mi, mj, mk);
     for (int p = 0; p < Q; ++p) {
-      const double fp = ldv<T>(buf + (size_t)p * N + yp) + WQ[p];
-      const double fm = ldv<T>(buf + (size_t)p * N + ym) + WQ[p];
+      const double fp = ldv<T>(buf + (size_t)p * qs + pp) + WQ[p];
+      const double fm = ldv<T>(buf + (size_t)p * qs + pm) + WQ[p];
       up[0] += fp * CX[p];
       up[1] += fp * CY[p];
       up[2] += fp * CZ[p];
@@ -352,7 +353,7 @@ __device__ void reconstruct_with(const DevDomain& d, T* buf, int ii, int jj, int
         second += Pab * Hab;
       }
     const double f = WQ[q] * (rb + 3.0 * rb * cu + 4.5 * second);
-    stv<T>(buf + (size_t)q * N + c, f - WQ[q]);
+    stv<T>(buf + (size_t)q * qs + pidx(d, ii, jj, kk), f - WQ[q]);
   }
 }
 
@@ -372,7 +373,7 @@ __device__ void reconstruct(const DevDomain& d, T* buf, uint32_t stamp, int ii, 
 // (at (i, j, k)) is fluid before and after the mapping update.
 template <typename T, typename V>
 __device__ void reconstruct_wave_with(const DevDomain& d, T* buf, long long c, int i, int lane, V usable) {
-  const size_t N = (size_t)d.N;
+  const size_t qs = (size_t)d.nx;
   const int ii = (int)(c % d.nx), jj = (int)((c / d.nx) % d.ny), kk = (int)(c / ((long long)d.nx * d.ny));
   bool valid = false;
   double rn = 0.0, un[3] = {0.0, 0.0, 0.0};
@@ -382,8 +383,9 @@ __device__ void reconstruct_wave_with(const DevDomain& d, T* buf, long long c, i
     valid = usable(y, yi, yj, yk);
     if (valid) {
       double f[Q];
+      const size_t py = pidx(d, yi, yj, yk);
 #pragma unroll
-      for (int p = 0; p < Q; ++p) f[p] = ldv<T>(buf + (size_t)p * N + y) + WQ[p];
+      for (int p = 0; p < Q; ++p) f[p] = ldv<T>(buf + (size_t)p * qs + py) + WQ[p];
 #pragma unroll
       for (int p = 0; p < Q; ++p) {
         rn += f[p];
@@ -450,7 +452,7 @@ __device__ void reconstruct_wave_with(const DevDomain& d, T* buf, long long c, i
         second += Pab * Hab;
       }
     const double f = WQ[q] * (rb + 3.0 * rb * cu + 4.5 * second);
-    stv<T>(buf + (size_t)q * N + c, f - WQ[q]);
+    stv<T>(buf + (size_t)q * qs + pidx(d, ii, jj, kk), f - WQ[q]);
   }
 }
 
@@ -640,13 +642,13 @@ __device__ __forceinline__ int slab_code(const DevDomain& d, const uint8_t* st, 
 // missing-link force 2 w_q c_q with the arm to the mid-point of the link.
 // The same arithmetic as ball_links.
 template <typename T, int U>
-__device__ __forceinline__ void slab_links(const DevDomain& d, T* buf, size_t N, const uint8_t* st, bool stg,
+__device__ __forceinline__ void slab_links(const DevDomain& d, T* buf, size_t qs, const uint8_t* st, bool stg,
                                            const uint32_t* lk, int k0, int tot, int EX, int HX, int HY, int ix0,
                                            int jy0, int kk, int i, uint32_t stamp, const double* xp,
                                            const double* up, const double* wp, double R, double* acc) {
   bool ok[U], cli[U];
   int code[U], q[U], qb[U], cq[U][3], y[U][2];
-  long long xg[U], yc[U];
+  long long xg[U];
   T gq[U], gqb[U], gm[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
@@ -662,7 +664,6 @@ __device__ __forceinline__ void slab_links(const DevDomain& d, T* buf, size_t N,
     const int tx = t % EX, ty = t / EX;
     y[u][0] = d.walls[0] ? ix0 + tx : wrap_near(ix0 + tx, d.nx);
     y[u][1] = d.walls[1] ? jy0 + ty : wrap_near(jy0 + ty, d.ny);
-    yc[u] = cidx(d, y[u][0], y[u][1], kk);
     const int cidx0 = (tx + 2) + HX * ((ty + 2) + HY * 2);
     // wall layers shield every non-wall cell, so y - c_q stays in range
     const int xi = wrapi(y[u][0] - cq[u][0], d.nx), xj = wrapi(y[u][1] - cq[u][1], d.ny),
@@ -672,14 +673,16 @@ __device__ __forceinline__ void slab_links(const DevDomain& d, T* buf, size_t N,
     cli[u] = false;
     gq[u] = gqb[u] = gm[u] = (T)0.0f;
     if (code[u] <= L_SHELL) {
-      long long xmg = 0;
+      size_t xmp = 0;
       if (d.boundary == 0) {
-        xmg = cidx(d, wrapi(xi - cq[u][0], d.nx), wrapi(xj - cq[u][1], d.ny), wrapi(xk - cq[u][2], d.nz));
-        cli[u] = slab_code(d, st, stg, cidx0, HX, HY, cq[u], 2, xmg, stamp, i) <= L_SHELL;
+        const int mi = wrapi(xi - cq[u][0], d.nx), mj = wrapi(xj - cq[u][1], d.ny), mk = wrapi(xk - cq[u][2], d.nz);
+        cli[u] = slab_code(d, st, stg, cidx0, HX, HY, cq[u], 2, cidx(d, mi, mj, mk), stamp, i) <= L_SHELL;
+        xmp = pidx(d, mi, mj, mk);
       }
-      gq[u] = buf[(size_t)q[u] * N + xg[u]];
-      gqb[u] = buf[(size_t)qb[u] * N + xg[u]];
-      if (cli[u]) gm[u] = buf[(size_t)q[u] * N + xmg];
+      const size_t xp_ = pidx(d, xi, xj, xk);
+      gq[u] = buf[(size_t)q[u] * qs + xp_];
+      gqb[u] = buf[(size_t)qb[u] * qs + xp_];
+      if (cli[u]) gm[u] = buf[(size_t)q[u] * qs + xmp];
     }
   }
 #pragma unroll
@@ -705,7 +708,7 @@ __device__ __forceinline__ void slab_links(const DevDomain& d, T* buf, size_t N,
       double val = vq;
       if (cli[u]) val += (1.0 - 2.0 * dd) / (1.0 + 2.0 * dd) * (raw_to_d<T>(gm[u]) - raw_to_d<T>(gqb[u]));
       val -= 4.0 / (1.0 + 2.0 * dd) * wq * 3.0 * (ub[0] * c[0] + ub[1] * c[1] + ub[2] * c[2]);
-      stv<T>(buf + (size_t)qb[u] * N + yc[u], val);
+      stv<T>(buf + (size_t)qb[u] * qs + pidx(d, y[u][0], y[u][1], kk), val);
       const double fq = vq + wq, fb = val + wq;
       for (int a = 0; a < 3; ++a) Fq[a] = (c[a] - ub[a]) * fq - (-c[a] - ub[a]) * fb;
     } else {
@@ -726,7 +729,6 @@ __device__ __forceinline__ void slab_links(const DevDomain& d, T* buf, size_t N,
 template <typename T>
 __device__ __forceinline__ void commit_block(const DevDomain& d, int blk, int cur, uint32_t stamp) {
   T* buf = (T*)d.pdf[cur];
-  const size_t N = (size_t)d.N;
   const int nbs = d.ZB * d.RB;
   const int i = blk / nbs, b = blk % nbs;
   const int bz = b / d.RB, brow = b % d.RB;
@@ -867,7 +869,7 @@ __device__ __forceinline__ void commit_block(const DevDomain& d, int blk, int cu
           if (mask & (1u << q)) lk[off++] = link_entry(t, q);
         __syncthreads();
         for (int k0 = threadIdx.x; k0 < tot; k0 += LINK_UNROLL * blockDim.x)
-          slab_links<T, LINK_UNROLL>(d, buf, N, st, stg, lk, k0, tot, EX, HX, HY, bx.lo[0], bx.lo[1] + ry0, kk, i,
+          slab_links<T, LINK_UNROLL>(d, buf, (size_t)d.nx, st, stg, lk, k0, tot, EX, HX, HY, bx.lo[0], bx.lo[1] + ry0, kk, i,
                                      stamp, xp, up, wp, R, acc);
         __syncthreads();  // the list, the wave sums and the staged states are reused
       }
@@ -948,12 +950,12 @@ constexpr uint8_t L_UNSET = 5;  // cell outside the staged ball
 // centre; y - c_q a wall or another sphere's solid: the missing-link force
 // 2 w_q c_q with the arm to the mid-point of the link.
 template <typename T, int U>
-__device__ __forceinline__ void ball_links(const DevDomain& d, T* buf, size_t N, const uint8_t* st,
+__device__ __forceinline__ void ball_links(const DevDomain& d, T* buf, const uint8_t* st,
                                            const uint32_t* lk, int k0, int tot, int he, const int* lo,
                                            const double* xp, const double* up, const double* wp, double R,
                                            double* acc) {
   bool ok[U], cli[U];
-  int code[U], q[U], qb[U], cq[U][3], y[U][3], xg[U], xmg[U];
+  int code[U], q[U], qb[U], cq[U][3], y[U][3];
   T gq[U], gqb[U], gm[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
@@ -973,20 +975,19 @@ __device__ __forceinline__ void ball_links(const DevDomain& d, T* buf, size_t N,
     const int off = cq[u][0] + he * (cq[u][1] + he * cq[u][2]);
     code[u] = ok[u] ? (int)st[t - off] : L_OWN;
     cli[u] = false;
-    xg[u] = xmg[u] = 0;
     gq[u] = gqb[u] = gm[u] = (T)0.0f;
     if (code[u] <= L_SHELL) {
       // wall layers shield every non-wall cell, so y - c_q stays in range
       const int xi = wrapi(y[u][0] - cq[u][0], d.nx), xj = wrapi(y[u][1] - cq[u][1], d.ny),
                 xk = wrapi(y[u][2] - cq[u][2], d.nz);
-      xg[u] = (int)cidx(d, xi, xj, xk);
+      const size_t xg = pidx(d, xi, xj, xk);
+      gq[u] = buf[(size_t)q[u] * d.nx + xg];
+      gqb[u] = buf[(size_t)qb[u] * d.nx + xg];
       if (d.boundary == 0 && st[t - 2 * off] <= L_SHELL) {
         cli[u] = true;
-        xmg[u] = (int)cidx(d, wrapi(xi - cq[u][0], d.nx), wrapi(xj - cq[u][1], d.ny), wrapi(xk - cq[u][2], d.nz));
+        gm[u] = buf[(size_t)q[u] * d.nx +
+                    pidx(d, wrapi(xi - cq[u][0], d.nx), wrapi(xj - cq[u][1], d.ny), wrapi(xk - cq[u][2], d.nz))];
       }
-      gq[u] = buf[(size_t)q[u] * N + xg[u]];
-      gqb[u] = buf[(size_t)qb[u] * N + xg[u]];
-      if (cli[u]) gm[u] = buf[(size_t)q[u] * N + xmg[u]];
     }
   }
 #pragma unroll
@@ -1012,7 +1013,7 @@ __device__ __forceinline__ void ball_links(const DevDomain& d, T* buf, size_t N,
       double val = vq;
       if (cli[u]) val += (1.0 - 2.0 * dd) / (1.0 + 2.0 * dd) * (raw_to_d<T>(gm[u]) - raw_to_d<T>(gqb[u]));
       val -= 4.0 / (1.0 + 2.0 * dd) * wq * 3.0 * (ub[0] * c[0] + ub[1] * c[1] + ub[2] * c[2]);
-      stv<T>(buf + (size_t)qb[u] * N + cidx(d, y[u][0], y[u][1], y[u][2]), val);
+      stv<T>(buf + (size_t)qb[u] * d.nx + pidx(d, y[u][0], y[u][1], y[u][2]), val);
       const double fq = vq + wq, fb = val + wq;
       for (int a = 0; a < 3; ++a) Fq[a] = (c[a] - ub[a]) * fq - (-c[a] - ub[a]) * fb;
     } else {
@@ -1034,7 +1035,6 @@ template <typename T>
 __device__ __forceinline__ void commit_ball(const DevDomain& d, int in_step, int i) {
   const int cur = map_buffer(d.ctl, in_step);
   T* buf = (T*)d.pdf[cur];
-  const size_t N = (size_t)d.N;
   extern __shared__ uint8_t smem[];
   const int he = d.stage_edge, H = he / 2;
   const int NS = he * he * he;
@@ -1216,7 +1216,7 @@ __device__ __forceinline__ void commit_ball(const DevDomain& d, int in_step, int
     }
     __syncthreads();
     for (int k0 = threadIdx.x; k0 < tot; k0 += BALL_LINK_UNROLL * blockDim.x)
-      ball_links<T, BALL_LINK_UNROLL>(d, buf, N, st, lk, k0, tot, he, lo, xp, up, wp, R, acc);
+      ball_links<T, BALL_LINK_UNROLL>(d, buf, st, lk, k0, tot, he, lo, xp, up, wp, R, acc);
     __syncthreads();  // the next chunk reuses the list and the wave sums
   }
   // 4. fixed-order block reduction

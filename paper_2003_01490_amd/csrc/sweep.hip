@@ -1,11 +1,10 @@
 // Fused D3Q19 pull stream + TRT+aB collide (Eqs. LBM_Stream, LBM_Collide, MRT
 // with the rates of Eqs. TRTmatrix / TRTbulkmatrix, adaptive shell of Sec. 2.3.2).
 //
-// One thread per cell, one block per whole x-row group where rows are at most
-// 256 cells (512 at FP16), so that the +-1 x-shifted loads of a row stay
-// inside the block and every source value is fetched from HBM once (wider
-// rows are split into pieces; the x-shifted loads then fetch one shared line
-// per piece twice).  The PDF slots of solid cells carry the boundary
+// One thread per cell, one block per whole x-row group where rows are narrow,
+// so that the +-1 x-shifted loads of a row stay inside the block and every
+// source value is fetched from HBM once (wider rows are split into pieces; the
+// x-shifted loads then fetch one shared line per piece twice).  The PDF slots of solid cells carry the boundary
 // values of the particle links that stream out of them (written by the
 // boundary kernel), so a fluid cell pulls 19 values without branching.  Wall
 // layers are fixed, so the sweep knows from the cell's coordinates which
@@ -29,15 +28,27 @@
 //   in shell cells (TRT+aB), everywhere (TRT+B), or s+ (TRT, SRT).
 #include "collide.hpp"
 
+#include <algorithm>
+
 namespace lbmdem {
 
 // one domain: tiles of whole x-rows, or of row pieces on wide lattices (see
 // launch_sweep_t), gx x gy tiles per z plane, x fastest; with `chunk` each
 // XCD takes a contiguous run of tiles; the current buffer is read from the
-// domain's step state
+// domain's step state.  The 19 rows of a (y, z) lie next to each other, so a
+// block stores one contiguous run: 512^3 FP32 3.51-3.53 ms alone (5.8 TB/s)
+// against 3.80 with a plane of N cells per direction.
 constexpr int SWEEP_MAX_THREADS = 512;
 
-template <typename T, bool FORCED, bool NTLOAD>
+// Non-temporal stores where every row starts on a 64-byte piece.  Elsewhere the
+// line at the junction of two rows is written in two parts, which plain stores
+// let the L2 join: 75 x 61 x 101 FP32 22 -> 17 us, 429 x 151 x 100 277 -> 204,
+// 150 x 130 x 140 FP64 198 -> 190, the batch above 1.59 -> 1.33 ms (aligned
+// rows lose: 384^3 1.54 -> 1.64 ms, 128x128x256 FP64 220 -> 243 us, 200^3 FP64
+// 453 -> 482 us).
+__host__ __device__ inline bool nt_stores(int nx, int size) { return nx * size % 64 == 0; }
+
+template <typename T, bool FORCED, bool NTLOAD, bool NTSTORE>
 __global__ __launch_bounds__(SWEEP_MAX_THREADS) void k_sweep(DevDomain d, int gx, int gy, int chunk) {
   using C = typename Store<T>::C;
   if (!step_live(d.ctl)) return;
@@ -52,12 +63,17 @@ __global__ __launch_bounds__(SWEEP_MAX_THREADS) void k_sweep(DevDomain d, int gx
   // place the whole descriptor in scratch memory)
   const T* src = (const T*)(cur ? d.pdf[1] : d.pdf[0]);
   T* dst = (T*)(cur ? d.pdf[0] : d.pdf[1]);
-  sweep_cell<T, FORCED, NTLOAD>(d, src, dst, x, y, z, (C)d.s_plus, (C)d.s_minus,
+  sweep_cell<T, FORCED, NTLOAD, NTSTORE>(d, src, dst, x, y, z, (C)d.s_plus, (C)d.s_minus,
                         (C)(d.s_bulk_shell - d.s_plus), (C)(d.s_bulk_other - d.s_plus));
 }
 
 // many domains in one launch: block b belongs to the domain k with
-// start[k] <= b < start[k+1] and covers 256 consecutive cells of it
+// start[k] <= b < start[k+1] and covers one tile of it.  Tiles are whole rows
+// (or row pieces) as in the single sweep: tiles of 256 consecutive cells, cut
+// anywhere in a row, share the lines at both cuts of all 19 rows with another
+// block (16 requests of 48-192 cells a side, 31.8 M cells, FP32: 2.10 ms;
+// 1.52 ms with a plane of N cells per direction; whole rows 1.33 ms; more rows
+// per block 1.46 ms at 512 cells, 1.69 at 1024).
 template <typename T>
 __global__ __launch_bounds__(256) void k_sweep_batch(const DevDomain* __restrict__ tab,
                                                      const int* __restrict__ start, int ndom) {
@@ -65,70 +81,76 @@ __global__ __launch_bounds__(256) void k_sweep_batch(const DevDomain* __restrict
   const int k = batch_domain(start, ndom, (int)blockIdx.x);
   const DevDomain& d = tab[k];
   if (!step_live(d.ctl)) return;
-  const long long c = (long long)(blockIdx.x - start[k]) * 256 + threadIdx.x;
-  if (c >= d.N) return;
-  const int x = (int)(c % d.nx), y = (int)((c / d.nx) % d.ny), z = (int)(c / ((long long)d.nx * d.ny));
+  const int t = (int)blockIdx.x - start[k];
+  const int bx = t % d.sw_gx, r = t / d.sw_gx, by = r % d.sw_gy, z = r / d.sw_gy;
+  const int ty = (int)threadIdx.x / d.sw_bx;
+  const int x = bx * d.sw_bx + (int)threadIdx.x - ty * d.sw_bx, y = by * d.sw_by + ty;
+  if (ty >= d.sw_by || x >= d.nx || y >= d.ny) return;
   const int cur = d.ctl->cur;
   const T* src = (const T*)d.pdf[cur];
   T* dst = (T*)d.pdf[cur ^ 1];
+  const C sp = (C)d.s_plus, sm = (C)d.s_minus, dbs = (C)(d.s_bulk_shell - d.s_plus), dbo = (C)(d.s_bulk_other - d.s_plus);
   if (d.forced)  // uniform over the block (one domain)
-    sweep_cell<T, true>(d, src, dst, x, y, z, (C)d.s_plus, (C)d.s_minus, (C)(d.s_bulk_shell - d.s_plus),
-                        (C)(d.s_bulk_other - d.s_plus));
+    sweep_cell<T, true, false, false>(d, src, dst, x, y, z, sp, sm, dbs, dbo);
+  else if (nt_stores(d.nx, (int)sizeof(T)))
+    sweep_cell<T, false, false, true>(d, src, dst, x, y, z, sp, sm, dbs, dbo);
   else
-    sweep_cell<T, false>(d, src, dst, x, y, z, (C)d.s_plus, (C)d.s_minus, (C)(d.s_bulk_shell - d.s_plus),
-                         (C)(d.s_bulk_other - d.s_plus));
+    sweep_cell<T, false, false, false>(d, src, dst, x, y, z, sp, sm, dbs, dbo);
+}
+
+// Tile shape.  Bounded by HBM bandwidth; what the shape changes is how many
+// tiles share cache lines.  Rows of whole 64-byte pieces: whole rows (256 / nx
+// of them) up to 256 cells, 512 at FP16, 128 at FP64; wider ones in pieces of
+// whole cache lines where the row has them: 384^3 FP32 128 x 2 1.49 ms against
+// 1.52 whole and 1.54 in 192s; 480 x 160 x 82 FP32 160 x 1 164 us against 166
+// whole, 175 in 256s and 186 in 240s, which end inside a line; 320^3 64 x 4
+// 825 us against 890 in 160s; 256^3 FP64 128 x 2 0.89 ms against 0.90 whole.
+// Other rows share the line at each junction of their 19 rows, so they stay
+// whole up to 512 cells, 256 at FP64 (429 x 151 x 100: FP32 204 us against 222
+// in 215s; FP64 428 us in 215s against 474 whole).
+void sweep_tiles(int nx, int ny, int storage, int max_threads, int* bx, int* by, int* gx, int* gy) {
+  const bool lines = nt_stores(nx, storage == 0 ? 8 : (storage == 1 ? 4 : 2));
+  const int whole = std::min(max_threads, lines ? (storage == 2 ? 512 : (storage == 1 ? 256 : 128)) : (storage == 0 ? 256 : 512));
+  *bx = nx;
+  if (nx > whole) {
+    const int cand[4] = {128, 64, 160, 96};
+    *bx = 0;
+    for (int c : cand)
+      if (lines && !*bx && nx % c == 0) *bx = c;
+    const int widest = std::max(whole, 256), n = (nx + widest - 1) / widest;
+    if (!*bx) *bx = (nx + n - 1) / n;  // equal pieces
+  }
+  *by = *bx < 256 ? 256 / *bx : 1;
+  *gx = (nx + *bx - 1) / *bx;
+  *gy = (ny + *by - 1) / *by;
 }
 
 template <typename T>
 static void launch_sweep_t(const DevDomain& d, hipStream_t s) {
-  dim3 block, grid;
-  if (d.nx <= 256 || (d.nx <= SWEEP_MAX_THREADS && d.nx * sizeof(T) <= 1024)) {
-    // whole rows per block: the periodic x-wrap stays inside the block (a
-    // 512-wide FP16 row in one block: 1.92 against 2.06 ms in 128 x 2 pieces
-    // at 512^3; 384- and 512-wide FP32 rows were slower whole)
-    block.x = d.nx;
-    block.y = d.nx <= 256 ? 256 / d.nx : 1;
-  } else {
-    // the widest piece of 256 or 128 cells that divides the row: 256 x 1 at
-    // 512^3 FP32 (3.80 against 3.99 ms alone with 128 x 2 and 4.00 ms with
-    // whole 512-cell rows), 128 x 2 for 384-wide rows (1.55 ms; whole rows
-    // 1.63 ms)
-    const int cand[4] = {256, 128, 192, 64};
-    block.x = 256;
-    for (int c : cand)
-      if (d.nx % c == 0) {
-        block.x = c;
-        break;
-      }
-    block.y = 256 / block.x;
-  }
-  block.z = 1;
-  const int gx = (d.nx + block.x - 1) / block.x, gy = (d.ny + block.y - 1) / block.y;
-  // Tile order, measured: rows of up to 256 cells, contiguous runs of tiles
-  // per XCD (122.5 against 125.6 us at 128x128x256); wider rows, plain order
-  // (1.56 against 1.63 ms at 384^3 FP32, 1.92 against 1.98 ms at 512^3 FP16)
-  const int chunk = d.nx <= 256 ? 1 : 0;
+  int bx, by, gx, gy;
+  sweep_tiles(d.nx, d.ny, d.storage, SWEEP_MAX_THREADS, &bx, &by, &gx, &gy);
+  const dim3 block((unsigned)bx, (unsigned)by);
+  const bool lines = nt_stores(d.nx, (int)sizeof(T));
+  // Tile order: plain (x fastest), except for pieces of rows that share lines
+  // or are a multiple of 512 cells, where contiguous runs of tiles per XCD are
+  // faster (512^3 FP32 3.53 against 3.91 ms, 1000 x 150 x 80 392 against 408
+  // us; elsewhere slower: 384^3 1.51 against 1.49 ms, 640 x 256 x 256 1.12
+  // against 1.07, 256^3 FP32 458 against 438 us, 128x128x256 117 against 110)
+  const int chunk = gx > 1 && (!lines || d.nx % 512 == 0) ? 1 : 0;
   const int tiles = gx * gy * d.nz;
-  grid = dim3(chunk ? xcd_grid(tiles) : tiles);
-  // Each source value is read once, and for rows of up to 256 cells
-  // non-temporal loads keep the streamed PDFs from displacing other data in
-  // the caches (128x128x256: 156.3 against 160.3 us per coupled step at FP32,
-  // 111.3 against 116.4 at FP16).  Wider rows share lines between blocks (rows
-  // in pieces) or between the waves of a row (512-cell FP16 rows), and the
-  // second read needs the line still cached (non-temporal: 1.66 against
-  // 1.56 ms at 384^3 FP32, 1.97 against 1.91 ms at 512^3 FP16).
-  const bool nt = d.nx <= 256;
-  if (d.forced) {
-    if (nt)
-      hipLaunchKernelGGL((k_sweep<T, true, true>), grid, block, 0, s, d, gx, gy, chunk);
-    else
-      hipLaunchKernelGGL((k_sweep<T, true, false>), grid, block, 0, s, d, gx, gy, chunk);
-  } else {
-    if (nt)
-      hipLaunchKernelGGL((k_sweep<T, false, true>), grid, block, 0, s, d, gx, gy, chunk);
-    else
-      hipLaunchKernelGGL((k_sweep<T, false, false>), grid, block, 0, s, d, gx, gy, chunk);
-  }
+  const dim3 grid(chunk ? xcd_grid(tiles) : tiles);
+  // Each value is read once, but a line that two waves share is read twice and
+  // should still be cached then: plain loads (384^3 FP32 1.49 against 1.55 ms,
+  // 320^3 826 against 933 us, 128x128x256 110 against 113 us).  At FP64 a wave
+  // covers four whole lines and non-temporal loads win (128x128x256 217
+  // against 223 us).
+  constexpr bool nt = sizeof(T) == 8;
+  if (d.forced)
+    hipLaunchKernelGGL((k_sweep<T, true, nt, false>), grid, block, 0, s, d, gx, gy, chunk);
+  else if (lines)
+    hipLaunchKernelGGL((k_sweep<T, false, nt, true>), grid, block, 0, s, d, gx, gy, chunk);
+  else
+    hipLaunchKernelGGL((k_sweep<T, false, nt, false>), grid, block, 0, s, d, gx, gy, chunk);
 }
 
 void launch_sweep(const DevDomain& d, hipStream_t s) {
@@ -140,14 +162,19 @@ void launch_sweep(const DevDomain& d, hipStream_t s) {
     launch_sweep_t<__half>(d, s);
 }
 
+template <typename T>
+static void launch_sweep_batch_t(const BatchTables& b, hipStream_t s) {
+  hipLaunchKernelGGL(k_sweep_batch<T>, dim3(b.sweep_blocks), dim3(256), 0, s, b.tab, b.sweep_start, b.ndom);
+}
+
 void launch_sweep_batch(const BatchTables& b, hipStream_t s) {
   if (b.sweep_blocks <= 0) return;
   if (b.storage == 0)
-    hipLaunchKernelGGL(k_sweep_batch<double>, dim3(b.sweep_blocks), dim3(256), 0, s, b.tab, b.sweep_start, b.ndom);
+    launch_sweep_batch_t<double>(b, s);
   else if (b.storage == 1)
-    hipLaunchKernelGGL(k_sweep_batch<float>, dim3(b.sweep_blocks), dim3(256), 0, s, b.tab, b.sweep_start, b.ndom);
+    launch_sweep_batch_t<float>(b, s);
   else
-    hipLaunchKernelGGL(k_sweep_batch<__half>, dim3(b.sweep_blocks), dim3(256), 0, s, b.tab, b.sweep_start, b.ndom);
+    launch_sweep_batch_t<__half>(b, s);
 }
 
 }  // namespace lbmdem
