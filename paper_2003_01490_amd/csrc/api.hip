@@ -611,6 +611,7 @@ int32_t lbmdem_create(const lbmdem_config* cfg, void* dev_buf, size_t dev_bytes,
     if (d.fused || d.map_ball) mbin_dims(*cfg, d.mbins.n);
     else d.mbins.n[0] = d.mbins.n[1] = d.mbins.n[2] = 1;
     d.mbins.cell = (int*)(base + L.mbins);
+    d.reach = cfg->max_radius + cfg->delta_ab;
     d.stage32 = (uint32_t*)(base + L.stage);
   }
   d.status = (int*)(base + L.status);
@@ -903,16 +904,16 @@ static int32_t step_direct(lbmdem_domain* dom, int32_t nsteps) {
       });
     };
     if (!ov) {
-      timed(dom, 0, s, [&] { launch_sweep(dom->d, s); });
+      timed(dom, 0, s, [&] { launch_sweep(dom->d, false, s); });
       dem();
     } else {
       dem();
       if (sw.a) {
-        launch_sweep(dom->d, s);
+        launch_sweep(dom->d, true, s);
         HIPCHK(dom, hipEventRecord(sw.b, s));
         dom->pending.push_back(sw);
       } else {
-        launch_sweep(dom->d, s);
+        launch_sweep(dom->d, true, s);
       }
       HIPCHK(dom, hipEventRecord(dom->ev_join, ds));
       HIPCHK(dom, hipStreamWaitEvent(s, dom->ev_join, 0));

@@ -172,6 +172,7 @@ struct DevDomain {
   double* slot;          // [P][sl_per][6]
   uint32_t* slot_stamp;  // [P][sl_per]
   DevBins mbins;
+  double reach;          // largest R + delta_aB
   uint32_t* stage32;     // [N] cell states of a full mapping update (in the stage buffer)
 };
 
@@ -350,7 +351,8 @@ __device__ inline void step_control(const DevDomain& d) {
 void sweep_tiles(int nx, int ny, int storage, int max_threads, int* bx, int* by, int* gx, int* gy);
 
 // host-side launchers (implemented in the .hip files)
-void launch_sweep(const DevDomain& d, hipStream_t s);
+// beside: other kernels run beside it on a second stream
+void launch_sweep(const DevDomain& d, bool beside, hipStream_t s);
 // mapping update outside the step: the flags and owners of the current
 // positions (claims, or the geometric update of the ball pass), the
 // (reconstruction), the boundary values on the current buffer, then the new

@@ -125,8 +125,26 @@ void sweep_tiles(int nx, int ny, int storage, int max_threads, int* bx, int* by,
   *gy = (ny + *by - 1) / *by;
 }
 
+// LDS that a sweep block of so many threads asks for (and does not use) so that
+// at most `waves` wavefronts of the sweep are resident on a CU.  The sweep is
+// bound by bandwidth and needs no more; with eight of its waves on every SIMD
+// (60 VGPRs each at FP32) no registers are left for a DEM wave (130-240 VGPRs)
+// beside it, and the DEM chain waits for waves of the sweep to end together:
+// 24,000 spheres beside the 512^3 FP32 sweep, sub-cycle 213 -> 61 us, first
+// positions 1,000 -> 21 us, sweep 3.55 -> 3.52 ms; one sphere beside the
+// 128x128x256 sweep 111 -> 46 us (FP64 148 -> 46).  20 waves per CU at FP32 and
+// FP64; at FP16 (51 VGPRs) 24, where 20 slow the sweep (1.98 against 1.85 ms).
+// The batch's sweep, with few DEM blocks beside it, is faster without (1.36 ms;
+// 1.37 at 20, 1.46 at 16).
+static unsigned residency_lds(int threads, int waves) {
+  constexpr unsigned LDS_CU = 160u * 1024u;
+  const int per_block = (threads + 63) / 64;
+  const unsigned blocks = (unsigned)std::max(2, waves / per_block);
+  return (LDS_CU / (blocks + 1) + 1024u) & ~511u;
+}
+
 template <typename T>
-static void launch_sweep_t(const DevDomain& d, hipStream_t s) {
+static void launch_sweep_t(const DevDomain& d, bool beside, hipStream_t s) {
   int bx, by, gx, gy;
   sweep_tiles(d.nx, d.ny, d.storage, SWEEP_MAX_THREADS, &bx, &by, &gx, &gy);
   const dim3 block((unsigned)bx, (unsigned)by);
@@ -145,21 +163,22 @@ static void launch_sweep_t(const DevDomain& d, hipStream_t s) {
   // covers four whole lines and non-temporal loads win (128x128x256 217
   // against 223 us).
   constexpr bool nt = sizeof(T) == 8;
+  const unsigned lds = beside ? residency_lds(bx * by, sizeof(T) == 2 ? 24 : 20) : 0u;
   if (d.forced)
-    hipLaunchKernelGGL((k_sweep<T, true, nt, false>), grid, block, 0, s, d, gx, gy, chunk);
+    hipLaunchKernelGGL((k_sweep<T, true, nt, false>), grid, block, lds, s, d, gx, gy, chunk);
   else if (lines)
-    hipLaunchKernelGGL((k_sweep<T, false, nt, true>), grid, block, 0, s, d, gx, gy, chunk);
+    hipLaunchKernelGGL((k_sweep<T, false, nt, true>), grid, block, lds, s, d, gx, gy, chunk);
   else
-    hipLaunchKernelGGL((k_sweep<T, false, nt, false>), grid, block, 0, s, d, gx, gy, chunk);
+    hipLaunchKernelGGL((k_sweep<T, false, nt, false>), grid, block, lds, s, d, gx, gy, chunk);
 }
 
-void launch_sweep(const DevDomain& d, hipStream_t s) {
+void launch_sweep(const DevDomain& d, bool beside, hipStream_t s) {
   if (d.storage == 0)
-    launch_sweep_t<double>(d, s);
+    launch_sweep_t<double>(d, beside, s);
   else if (d.storage == 1)
-    launch_sweep_t<float>(d, s);
+    launch_sweep_t<float>(d, beside, s);
   else
-    launch_sweep_t<__half>(d, s);
+    launch_sweep_t<__half>(d, beside, s);
 }
 
 template <typename T>
