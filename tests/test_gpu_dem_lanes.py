@@ -72,3 +72,50 @@ def test_many_partners_of_one_sphere(lub_mask):
                                                         "T_fp", "T_raw")}), f"sphere {i}")
     a, b = gs[0].spheres(), gs[1].spheres()
     assert all(np.array_equal(a[k], b[k]) for k in a), "the two kernels differ"
+
+
+@pytest.mark.parametrize("count", [1, 40])
+def test_overlap_equals_sequential_behind_a_long_sweep(count):
+    """The DEM beside the sweep gives the bits of the sequential step on a
+    lattice whose sweep is long enough for the second stream to be used (about
+    90 us), by direct launches and by a step graph."""
+    import torch
+
+    from paper_2003_01490_amd import lbmdem as L
+
+    stream = torch.cuda.Stream()
+    wl = W.dense(count, nxyz=(128, 128, 192), count=count, D=8.0, min_gap=0.2, u_rms=0.05, nu=0.01)
+    print(f"[case] overlap vs sequential, 128x128x192, {count} spheres, FP32", flush=True)
+    gs = [gpu_domain(wl, storage=L.STORE_F32, stream=stream, overlap=o) for o in (1, 0, 1)]
+    gs[2].set_graph(True)
+    for g in gs:
+        g.step(15)
+        g.step(15)
+    ref = gs[1].spheres()
+    for g in (gs[0], gs[2]):
+        s = g.spheres()
+        assert all(np.array_equal(s[k], ref[k]) for k in s)
+        assert np.array_equal(g.field("pdf_raw"), gs[1].field("pdf_raw"))
+        assert np.array_equal(g.field("flags"), gs[1].field("flags"))
+
+
+@pytest.mark.parametrize("count,n", [(60, 30), (150, 40)])
+def test_geometric_mapping_in_a_crowd(count, n):
+    """Spheres of D = 5 nearly in contact, in a box only a few bins wide
+    (periodic wrap of the gathered neighbours): the one-block-per-sphere pass
+    against the oracle's mapping and state."""
+    wl = W.dense(count, n=n, count=count, D=5.0, min_gap=0.02, u_rms=0.1, nu=0.03)
+    print(f"[case] {count} spheres D=5 in {n}^3, ball pass, FP64", flush=True)
+    o, g = oracle_domain(wl), gpu_domain(wl, map_kernel=2)
+    for k in range(4):
+        o.step(3)
+        g.step(3)
+        co, oo = o.flags()
+        cg, og = g.flags()
+        assert np.array_equal(cg, co)
+        assert np.array_equal(og[co == 2], oo[co == 2])
+    F = max(float(np.abs(o.sphere(i)["F_tot"]).max()) for i in range(count))
+    for i in range(count):
+        check_all(sphere_errs(g.sphere(i), o.sphere(i), 5.0, {"u": 0.1, "F": F}),
+                  fp64_bounds(**{k: BOUND for k in ("x", "u", "w", "F_fp", "F_raw", "F_tot", "F_lub", "F_col",
+                                                    "T_fp", "T_raw")}), f"sphere {i}")
