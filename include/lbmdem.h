@@ -128,8 +128,10 @@ typedef struct lbmdem_config {
                                run on a second, library-owned stream beside the
                                sweep (they need only the previous step's
                                forces); it waits on and rejoins the domain's
-                               stream within the step.  0: everything on the
-                               domain's stream.  Results are identical.          */
+                               stream within the step; lattices whose sweep is
+                               too short to hide them run them after it.  0:
+                               everything on the domain's stream.  Results are
+                               identical.                                        */
   double body_force[3];     /* fluid body force a (force density, lattice units),
                                Guo's forcing in the collision (test scenarios of
                                Sec. 2.4 such as the Stokes-flow sphere array); it

@@ -827,8 +827,20 @@ int32_t lbmdem_set_sphere_mode(lbmdem_domain* dom, int32_t id, int32_t mode, con
 
 // The DEM sub-cycles and the claims of step t need the forces formed by the
 // boundary pass of step t - 1 and the particle state, not the sweep of step
-// t, so they can run on a second stream while the sweep runs.
-static bool overlap_step(const lbmdem_domain* dom) { return dom->cfg.overlap && dom->d.P > 0; }
+// t, so they can run on a second stream while the sweep runs.  Forking and
+// joining the streams costs a step 10-20 us of queue synchronisation (a few in
+// a captured graph), so a sweep too short to hide the DEM behind is followed
+// by it instead.  Per step, beside / after the sweep: direct launches 32^3 FP64
+// 65 / 48 us, 96x96x128 88 / 84, 96^3 FP64 with 156 spheres 300 / 283, 128^3
+// with 375 spheres 335 / 325, 128x128x256 144 / 163, 192^3 with 1,200 spheres
+// 484 / 512; graphs 32^3 49 / 49, 75x61x101 59 / 69, 96x96x128 76 / 89.  The
+// estimate is the sweep's bytes at 5.5 TB/s.
+constexpr double OVERLAP_MIN_US = 80.0, OVERLAP_MIN_US_GRAPH = 10.0;
+static bool overlap_step(const lbmdem_domain* dom, bool graph) {
+  if (!dom->cfg.overlap || dom->d.P <= 0) return false;
+  const double us = lbmdem_sweep_bytes(dom) / 5.5e6;
+  return us >= (graph ? OVERLAP_MIN_US_GRAPH : OVERLAP_MIN_US);
+}
 
 static int32_t ensure_side(lbmdem_domain* dom) {
   if (dom->side) return LBMDEM_OK;
@@ -847,7 +859,7 @@ static void drop_step_graph(lbmdem_domain* dom) {
 }
 
 // the launches of nsteps steps, enqueued directly
-static int32_t step_direct(lbmdem_domain* dom, int32_t nsteps) {
+static int32_t step_direct(lbmdem_domain* dom, int32_t nsteps, bool graph) {
   hipStream_t s0 = dom->stream;
   if (dom->d.fused) {
     // Alg. 1 in order on one stream: the sweep with the link boundary values
@@ -869,7 +881,7 @@ static int32_t step_direct(lbmdem_domain* dom, int32_t nsteps) {
     HIPCHK(dom, hipGetLastError());
     return LBMDEM_OK;
   }
-  const bool ov = overlap_step(dom);
+  const bool ov = overlap_step(dom, graph);
   if (ov && nsteps > 0)
     if (int32_t rc = ensure_side(dom)) return rc;
   hipStream_t s = dom->stream;
@@ -933,16 +945,16 @@ int32_t lbmdem_step(lbmdem_domain* dom, int32_t nsteps) {
   if (dom->failed) return fail(dom, LBMDEM_ESTATE, "domain has failed");
   if (dom->batch) return fail(dom, LBMDEM_EINVAL, "domain is stepped by its batch");
   dom->d.P = (int)dom->hR.size();
-  if (!dom->use_graph || dom->prof != 0 || nsteps == 0) return step_direct(dom, nsteps);
+  if (!dom->use_graph || dom->prof != 0 || nsteps == 0) return step_direct(dom, nsteps, false);
   // every kernel reads its step state (buffer parity, stamp, step count) from
   // device memory, so one captured step serves every step
   const int presc = dom->may_prescribe ? 1 : 0;
   if (!dom->gexec || dom->g_P != dom->d.P || dom->g_presc != presc) {
     drop_step_graph(dom);
-    if (overlap_step(dom))
+    if (overlap_step(dom, true))
       if (int32_t rc = ensure_side(dom)) return rc;
     HIPCHK(dom, hipStreamBeginCapture(dom->stream, hipStreamCaptureModeThreadLocal));
-    const int32_t rc = step_direct(dom, 1);
+    const int32_t rc = step_direct(dom, 1, true);
     hipGraph_t g = nullptr;
     const hipError_t e = hipStreamEndCapture(dom->stream, &g);
     if (rc != LBMDEM_OK || e != hipSuccess) {
