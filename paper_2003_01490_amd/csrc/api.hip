@@ -1094,48 +1094,57 @@ int32_t lbmdem_probe_density_static(lbmdem_domain* dom, int32_t n, const double*
   return LBMDEM_OK;
 }
 
+// whether a kernel of the domain's device may write to ptr: device memory of
+// that device, aligned for the type (anything else is reached by copies)
+static bool writable_here(const lbmdem_domain* dom, const void* ptr, size_t align) {
+  hipPointerAttribute_t at;
+  if ((uintptr_t)ptr % align != 0) return false;
+  if (hipPointerGetAttributes(&at, ptr) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return at.type == hipMemoryTypeDevice && at.device == dom->device;
+}
+
 int32_t lbmdem_get_field(lbmdem_domain* dom, int32_t field, void* dst, size_t bytes,
                          int32_t dst_is_device) {
   if (!dom || !dst) return LBMDEM_EINVAL;
   const size_t N = (size_t)dom->d.N;
-  size_t need = 0;
-  int first = 0, planes = 0;
+  size_t need = 0, align = 8;
+  int kind_of = FIELD_RHO, planes = 0;
   switch (field) {
-    case LBMDEM_FIELD_RHO: need = 8 * N; first = 0; planes = 1; break;
-    case LBMDEM_FIELD_VEL: need = 24 * N; first = 1; planes = 3; break;
-    case LBMDEM_FIELD_PDF: need = 8 * N * Q; first = 10; planes = Q; break;
-    case LBMDEM_FIELD_FLAGS: need = N; first = 40; planes = 1; break;
-    case LBMDEM_FIELD_OWNER: need = 4 * N; first = 41; planes = 1; break;
-    case LBMDEM_FIELD_PDF_RAW: need = 8 * N * Q; first = 60; planes = Q; break;
+    case LBMDEM_FIELD_RHO: need = 8 * N; kind_of = FIELD_RHO; planes = 1; break;
+    case LBMDEM_FIELD_VEL: need = 24 * N; kind_of = FIELD_VEL; planes = 3; break;
+    case LBMDEM_FIELD_PDF: need = 8 * N * Q; kind_of = FIELD_PDF; planes = Q; break;
+    case LBMDEM_FIELD_FLAGS: need = N; align = 1; break;
+    case LBMDEM_FIELD_OWNER: need = 4 * N; align = 4; break;
+    case LBMDEM_FIELD_PDF_RAW: need = 8 * N * Q; kind_of = FIELD_PDF_RAW; planes = Q; break;
     default: return fail(dom, LBMDEM_EINVAL, "unknown field");
   }
   if (bytes < need) return fail(dom, LBMDEM_EINVAL, "destination too small");
   double* stage = (double*)((char*)dom->region + dom->L.stage);
   hipStream_t st = dom->stream;
+  // device memory is written by the kernels themselves, everything else
+  // through the stage, a plane at a time
+  const bool direct = dst_is_device && writable_here(dom, dst, align);
   const hipMemcpyKind kind = dst_is_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
   if (field == LBMDEM_FIELD_FLAGS || field == LBMDEM_FIELD_OWNER) {
-    std::vector<double> h(N);
-    launch_fields(dom->d, first, stage, st);
+    void* to = direct ? dst : (void*)stage;
+    const bool flags = field == LBMDEM_FIELD_FLAGS;
+    launch_get_map(dom->d, flags ? (uint8_t*)to : nullptr, flags ? nullptr : (int32_t*)to, st);
     HIPCHK(dom, hipGetLastError());
-    HIPCHK(dom, hipMemcpyAsync(h.data(), stage, 8 * N, hipMemcpyDeviceToHost, st));
-    HIPCHK(dom, hipStreamSynchronize(st));
-    if (field == LBMDEM_FIELD_FLAGS) {
-      std::vector<uint8_t> o(N);
-      for (size_t c = 0; c < N; ++c) o[c] = (uint8_t)h[c];
-      HIPCHK(dom, hipMemcpy(dst, o.data(), N, dst_is_device ? hipMemcpyHostToDevice : hipMemcpyHostToHost));
-    } else {
-      std::vector<int32_t> o(N);
-      for (size_t c = 0; c < N; ++c) o[c] = (int32_t)h[c];
-      HIPCHK(dom, hipMemcpy(dst, o.data(), 4 * N, dst_is_device ? hipMemcpyHostToDevice : hipMemcpyHostToHost));
+    if (!direct) HIPCHK(dom, hipMemcpyAsync(dst, stage, need, kind, st));
+  } else if (direct) {
+    launch_fields(dom->d, kind_of, 0, planes, (double*)dst, st);
+    HIPCHK(dom, hipGetLastError());
+  } else {
+    for (int k = 0; k < planes; ++k) {
+      launch_fields(dom->d, kind_of, k, 1, stage, st);
+      HIPCHK(dom, hipGetLastError());
+      HIPCHK(dom, hipMemcpyAsync((char*)dst + 8 * N * (size_t)k, stage, 8 * N, kind, st));
     }
-    return LBMDEM_OK;
   }
-  for (int k = 0; k < planes; ++k) {
-    launch_fields(dom->d, first + k, stage, st);
-    HIPCHK(dom, hipGetLastError());
-    HIPCHK(dom, hipMemcpyAsync((char*)dst + 8 * N * (size_t)k, stage, 8 * N, kind, st));
-    HIPCHK(dom, hipStreamSynchronize(st));
-  }
+  HIPCHK(dom, hipStreamSynchronize(st));
   return LBMDEM_OK;
 }
 

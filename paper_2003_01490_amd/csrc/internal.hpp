@@ -386,7 +386,11 @@ constexpr int DEM_GRID_THREADS = 128;
 // 161 us in three rounds of 512 threads, the chain 107 us; 40 spheres 78 us
 // against about 100.
 constexpr int DEM_LDS_MAX = 64;
-void launch_fields(const DevDomain& d, int field, double* dst, hipStream_t s);
+// planes [first, first + count) of a whole-lattice field (N doubles each), and
+// the canonical flags or owners (either may be NULL), into device memory
+enum { FIELD_RHO, FIELD_VEL, FIELD_PDF, FIELD_PDF_RAW };
+void launch_fields(const DevDomain& d, int field, int first, int count, double* dst, hipStream_t s);
+void launch_get_map(const DevDomain& d, uint8_t* flags, int32_t* owner, hipStream_t s);
 void launch_set_pdf(const DevDomain& d, int q, const double* src, hipStream_t s);
 // direction q of PDF buffer buf to (out) or from a plane of N stored values
 void launch_plane_copy(const DevDomain& d, int buf, int q, void* plane, bool out, hipStream_t s);
