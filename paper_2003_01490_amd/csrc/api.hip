@@ -134,6 +134,23 @@ int rowblocks(const lbmdem_config& c) {
   return std::min(full, per);
 }
 
+// Boundary kernel of the slab pass: with one block per force partial where
+// the chip holds all those blocks at once (256 CUs, four each), a slab's rows
+// shared out over its RB blocks (one sphere of D = 8: 12.9 us, against 14.9 us
+// with all rows in one block).  Beyond that a block takes as many rows as fill
+// its 256 threads with cells: 40 spheres of D = 8 take 17.9 us in 720
+// blocks (40.3 us in 2160 blocks of eight rows with twice the registers).
+constexpr int COMMIT_RESIDENT = 4 * 256;
+
+void slab_geom(const lbmdem_config& c, DevDomain& d) {
+  const int w = 2 * (int)std::ceil(c.max_radius + c.delta_ab) + 3;  // cells across the shell ball
+  d.rows = COMMIT_ROWS;
+  if ((long long)std::max(c.max_spheres, 1) * d.ZB * d.RB > COMMIT_RESIDENT) d.rows = std::max(COMMIT_ROWS, 256 / w);
+  d.rowb = std::min(d.RB, (std::min(c.ny, w) + d.rows - 1) / d.rows);
+  d.cols = std::min(std::min(c.nx, box_extent(c)), 252);  // 256 threads stage a row and its halo
+  d.slab_bytes = 5 * (d.rows + 4) * (d.cols + 4);
+}
+
 // uniform bins of the many-sphere neighbour search: edge at least the largest
 // centre distance of two listed neighbours (2 R_max + cut-off + skin), grown
 // if the count would exceed a few per sphere
@@ -590,6 +607,7 @@ int32_t lbmdem_create(const lbmdem_config* cfg, void* dev_buf, size_t dev_bytes,
   d.P = 0;
   d.ZB = zblocks(*cfg);
   d.RB = rowblocks(*cfg);
+  slab_geom(*cfg, d);
   d.map_ball = use_ball(*cfg) ? 1 : 0;
   d.stage_edge = stage_edge(*cfg);
   d.list_cap = list_cap(*cfg);
@@ -1450,7 +1468,7 @@ static int32_t build_tables(lbmdem_batch* b) {
     const DevDomain& d = dom->d;
     ss[k + 1] = ss[k] + d.sw_gx * d.sw_gy * d.nz;
     cs[k + 1] = cs[k] + d.P * d.ZB;
-    ms[k + 1] = ms[k] + d.P * d.ZB * d.RB;
+    ms[k + 1] = ms[k] + d.P * d.ZB * d.rowb;
   }
   const size_t tb = align256(sizeof(DevDomain) * (size_t)std::max(nd, 1));
   const size_t ib = align256(4 * (size_t)(nd + 1));
@@ -1477,6 +1495,8 @@ static int32_t build_tables(lbmdem_batch* b) {
   b->t.sweep_blocks = ss[nd];
   b->t.claim_blocks = cs[nd];
   b->t.commit_blocks = ms[nd];
+  b->t.slab_bytes = 0;
+  for (const DevDomain& d : tab) b->t.slab_bytes = std::max(b->t.slab_bytes, d.slab_bytes);
   b->t.storage = b->storage;
   b->d_steps = (long long*)(m + tb + 3 * ib);
   b->d_stopped = (int*)(m + tb + 3 * ib + align256(8 * (size_t)std::max(nd, 1)));

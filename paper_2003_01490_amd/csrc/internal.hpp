@@ -30,7 +30,7 @@ constexpr uint8_t F_SOLID = 1;
 constexpr uint8_t F_WALL = 2;
 constexpr uint8_t F_SHELL = 4;
 
-constexpr int COMMIT_ROWS = 8;   // y-rows of a box slab per boundary block
+constexpr int COMMIT_ROWS = 8;   // y-rows of a box slab per force partial
 constexpr int HIST_SLOTS = 24;   // contact-history slots per sphere
 constexpr int NBR_MAX = 48;      // neighbour-list capacity per sphere
 
@@ -143,7 +143,10 @@ struct DevDomain {
   DevParticles p;
   int P;           // spheres present
   int ZB;          // mapping blocks per sphere along z (slabs)
-  int RB;          // row blocks per slab in the boundary kernel
+  int RB;          // force partials per slab
+  // boundary kernel of the slab pass: y-rows and x-columns of a chunk, row
+  // blocks per slab (<= RB), LDS bytes of a chunk's staged states
+  int rows, cols, rowb, slab_bytes;
   double* partial; // [P][ZB * RB][6]
   int map_ball;    // boundary pass: 1 one block per sphere (k_commit_ball), 0 slab blocks
   int stage_edge;  // edge of the LDS-staged cube of k_commit_ball (odd)
@@ -266,7 +269,8 @@ struct BatchTables {
   const DevDomain* tab;
   const int* sweep_start;   // sw_gx * sw_gy * nz blocks per domain
   const int* claim_start;   // P * ZB blocks per domain (claims, reconstruction)
-  const int* commit_start;  // P * ZB * RB sphere blocks per domain
+  const int* commit_start;  // P * ZB * rowb sphere blocks per domain
+  int slab_bytes;           // largest of the domains'
   int ndom;
   int max_P;  // most spheres in one domain
   int sweep_blocks, claim_blocks, commit_blocks;

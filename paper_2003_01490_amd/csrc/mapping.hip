@@ -45,7 +45,6 @@ namespace lbmdem {
 enum { S_FLUID = 0, S_SHELL = 1, S_SOLID = 2, S_WALL = 3 };
 // staged neighbour codes relative to the sphere a block works for
 enum { L_FLUID = 0, L_SHELL = 1, L_OWN = 2, L_OTHER = 3, L_WALL = 4 };
-constexpr int STAGE_BYTES = 32768;
 
 struct Box {
   int lo[3];
@@ -620,118 +619,83 @@ __device__ __forceinline__ uint32_t link_entry(int t, int q) {
          ((uint32_t)(CY[q] + 1) << 28) | ((uint32_t)(CZ[q] + 1) << 30);
 }
 
-constexpr int LINK_UNROLL = 2;       // links in flight per thread, slab pass
-constexpr int BALL_LINK_UNROLL = 1;  // ball pass: fewer registers, five waves per SIMD
-
-// State code of the cell z = y - m c_q seen from sphere i: from the staged
-// slab (index cidx0 of y, staged row pitch HX, HY) or from the global arrays.
-__device__ __forceinline__ int slab_code(const DevDomain& d, const uint8_t* st, bool stg, int cidx0, int HX,
-                                         int HY, const int* c, int m, long long zg, uint32_t stamp, int i) {
-  if (stg) return st[cidx0 - m * (c[0] + HX * (c[1] + HY * c[2]))];
-  int zo = -1;
-  const int zs = new_state(d, zg, stamp, &zo);
-  return zs == S_WALL ? L_WALL : (zs == S_SOLID ? (zo == i ? L_OWN : L_OTHER) : (zs == S_SHELL ? L_SHELL : L_FLUID));
-}
-
-// Links k0, k0 + blockDim.x, ... (at most U below tot) of one row chunk of
-// a slab block, all loads issued before any is used: the cell is entry bits
-// 0-15 = tx + EX ty of the chunk (plane kk, rows from jy0, columns from ix0).
-// y - c_q fluid: boundary value of Eq. (MEM_CLI) into slot qbar of y (delta =
-// 1/2 in the coefficients where y - 2 c_q is not fluid), force of Eq.
-// (MEM_Fq) and its torque; y - c_q a wall or another sphere's solid: the
-// missing-link force 2 w_q c_q with the arm to the mid-point of the link.
-// The same arithmetic as ball_links.
-template <typename T, int U>
-__device__ __forceinline__ void slab_links(const DevDomain& d, T* buf, size_t qs, const uint8_t* st, bool stg,
-                                           const uint32_t* lk, int k0, int tot, int EX, int HX, int HY, int ix0,
-                                           int jy0, int kk, int i, uint32_t stamp, const double* xp,
-                                           const double* up, const double* wp, double R, double* acc) {
-  bool ok[U], cli[U];
-  int code[U], q[U], qb[U], cq[U][3], y[U][2];
-  long long xg[U];
-  T gq[U], gqb[U], gm[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int k = k0 + u * (int)blockDim.x;
-    ok[u] = k < tot;
-    const uint32_t e = ok[u] ? lk[k] : 0u;
-    const int t = (int)(e & 0xFFFFu);
-    q[u] = (int)((e >> 16) & 31u);
-    qb[u] = (int)((e >> 21) & 31u);
-    cq[u][0] = (int)((e >> 26) & 3u) - 1;
-    cq[u][1] = (int)((e >> 28) & 3u) - 1;
-    cq[u][2] = (int)((e >> 30) & 3u) - 1;
-    const int tx = t % EX, ty = t / EX;
-    y[u][0] = d.walls[0] ? ix0 + tx : wrap_near(ix0 + tx, d.nx);
-    y[u][1] = d.walls[1] ? jy0 + ty : wrap_near(jy0 + ty, d.ny);
-    const int cidx0 = (tx + 2) + HX * ((ty + 2) + HY * 2);
+// Link e of sphere i, from the states staged in LDS as an HX x HY x ... box
+// whose first cell is o (unwrapped).  y - c_q fluid: boundary value of Eq.
+// (MEM_CLI) into slot qbar of y (delta = 1/2 in the coefficients where
+// y - 2 c_q is not fluid), force of Eq. (MEM_Fq) and its torque about the
+// centre; y - c_q a wall or another sphere's solid: the missing-link force
+// 2 w_q c_q with the arm to the mid-point of the link.
+template <typename T>
+__device__ __forceinline__ void sphere_link(const DevDomain& d, T* buf, const uint8_t* st, uint32_t e, int HX, int HY,
+                                            const int* o, const double* xp, const double* up, const double* wp,
+                                            double R, double* acc) {
+  const int t = (int)(e & 0xFFFFu), q = (int)((e >> 16) & 31u), qb = (int)((e >> 21) & 31u);
+  const int c[3] = {(int)((e >> 26) & 3u) - 1, (int)((e >> 28) & 3u) - 1, (int)((e >> 30) & 3u) - 1};
+  const int h[3] = {t % HX, (t / HX) % HY, t / (HX * HY)};
+  int y[3];
+  y[0] = d.walls[0] ? o[0] + h[0] : wrap_near(o[0] + h[0], d.nx);
+  y[1] = d.walls[1] ? o[1] + h[1] : wrap_near(o[1] + h[1], d.ny);
+  y[2] = d.walls[2] ? o[2] + h[2] : wrap_near(o[2] + h[2], d.nz);
+  const int off = c[0] + HX * (c[1] + HY * c[2]);
+  const double wq = c[0] * c[0] + c[1] * c[1] + c[2] * c[2] == 1 ? 1.0 / 18 : 1.0 / 36;
+  double Fq[3], arm[3];
+  if (st[t - off] <= L_SHELL) {
     // wall layers shield every non-wall cell, so y - c_q stays in range
-    const int xi = wrapi(y[u][0] - cq[u][0], d.nx), xj = wrapi(y[u][1] - cq[u][1], d.ny),
-              xk = wrapi(kk - cq[u][2], d.nz);
-    xg[u] = cidx(d, xi, xj, xk);
-    code[u] = ok[u] ? slab_code(d, st, stg, cidx0, HX, HY, cq[u], 1, xg[u], stamp, i) : L_OWN;
-    cli[u] = false;
-    gq[u] = gqb[u] = gm[u] = (T)0.0f;
-    if (code[u] <= L_SHELL) {
-      size_t xmp = 0;
-      if (d.boundary == 0) {
-        const int mi = wrapi(xi - cq[u][0], d.nx), mj = wrapi(xj - cq[u][1], d.ny), mk = wrapi(xk - cq[u][2], d.nz);
-        cli[u] = slab_code(d, st, stg, cidx0, HX, HY, cq[u], 2, cidx(d, mi, mj, mk), stamp, i) <= L_SHELL;
-        xmp = pidx(d, mi, mj, mk);
-      }
-      const size_t xp_ = pidx(d, xi, xj, xk);
-      gq[u] = buf[(size_t)q[u] * qs + xp_];
-      gqb[u] = buf[(size_t)qb[u] * qs + xp_];
-      if (cli[u]) gm[u] = buf[(size_t)q[u] * qs + xmp];
-    }
+    const int xi = wrapi(y[0] - c[0], d.nx), xj = wrapi(y[1] - c[1], d.ny), xk = wrapi(y[2] - c[2], d.nz);
+    const size_t xg = pidx(d, xi, xj, xk);
+    const T gq = buf[(size_t)q * d.nx + xg], gqb = buf[(size_t)qb * d.nx + xg];
+    T gm = (T)0.0f;
+    const bool cli = d.boundary == 0 && st[t - 2 * off] <= L_SHELL;
+    if (cli) gm = buf[(size_t)q * d.nx + pidx(d, wrapi(xi - c[0], d.nx), wrapi(xj - c[1], d.ny), wrapi(xk - c[2], d.nz))];
+    double r[3];
+    r[0] = min_image(((double)xi + 0.5) - xp[0], d.nx, d.walls[0]);
+    r[1] = min_image(((double)xj + 0.5) - xp[1], d.ny, d.walls[1]);
+    r[2] = min_image(((double)xk + 0.5) - xp[2], d.nz, d.walls[2]);
+    const double dl = link_delta(r, c, R);
+    for (int a = 0; a < 3; ++a) arm[a] = r[a] + dl * c[a];
+    double ub[3];
+    ub[0] = up[0] + (wp[1] * arm[2] - wp[2] * arm[1]);
+    ub[1] = up[1] + (wp[2] * arm[0] - wp[0] * arm[2]);
+    ub[2] = up[2] + (wp[0] * arm[1] - wp[1] * arm[0]);
+    const double dd = cli ? dl : 0.5;
+    const double vq = raw_to_d<T>(gq);
+    double val = vq;
+    if (cli) val += (1.0 - 2.0 * dd) / (1.0 + 2.0 * dd) * (raw_to_d<T>(gm) - raw_to_d<T>(gqb));
+    val -= 4.0 / (1.0 + 2.0 * dd) * wq * 3.0 * (ub[0] * c[0] + ub[1] * c[1] + ub[2] * c[2]);
+    stv<T>(buf + (size_t)qb * d.nx + pidx(d, y[0], y[1], y[2]), val);
+    const double fq = vq + wq, fb = val + wq;
+    for (int a = 0; a < 3; ++a) Fq[a] = (c[a] - ub[a]) * fq - (-c[a] - ub[a]) * fb;
+  } else {
+    for (int a = 0; a < 3; ++a) Fq[a] = 2.0 * wq * c[a];
+    arm[0] = min_image(((double)y[0] + 0.5) - xp[0], d.nx, d.walls[0]) - 0.5 * c[0];
+    arm[1] = min_image(((double)y[1] + 0.5) - xp[1], d.ny, d.walls[1]) - 0.5 * c[1];
+    arm[2] = min_image(((double)y[2] + 0.5) - xp[2], d.nz, d.walls[2]) - 0.5 * c[2];
   }
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    if (!ok[u]) continue;
-    const int* c = cq[u];
-    const double wq = c[0] * c[0] + c[1] * c[1] + c[2] * c[2] == 1 ? 1.0 / 18 : 1.0 / 36;
-    double Fq[3], arm[3];
-    if (code[u] <= L_SHELL) {
-      const int xi = wrapi(y[u][0] - c[0], d.nx), xj = wrapi(y[u][1] - c[1], d.ny), xk = wrapi(kk - c[2], d.nz);
-      double r[3];
-      r[0] = min_image(((double)xi + 0.5) - xp[0], d.nx, d.walls[0]);
-      r[1] = min_image(((double)xj + 0.5) - xp[1], d.ny, d.walls[1]);
-      r[2] = min_image(((double)xk + 0.5) - xp[2], d.nz, d.walls[2]);
-      const double dl = link_delta(r, c, R);
-      for (int a = 0; a < 3; ++a) arm[a] = r[a] + dl * c[a];
-      double ub[3];
-      ub[0] = up[0] + (wp[1] * arm[2] - wp[2] * arm[1]);
-      ub[1] = up[1] + (wp[2] * arm[0] - wp[0] * arm[2]);
-      ub[2] = up[2] + (wp[0] * arm[1] - wp[1] * arm[0]);
-      const double dd = cli[u] ? dl : 0.5;
-      const double vq = raw_to_d<T>(gq[u]);
-      double val = vq;
-      if (cli[u]) val += (1.0 - 2.0 * dd) / (1.0 + 2.0 * dd) * (raw_to_d<T>(gm[u]) - raw_to_d<T>(gqb[u]));
-      val -= 4.0 / (1.0 + 2.0 * dd) * wq * 3.0 * (ub[0] * c[0] + ub[1] * c[1] + ub[2] * c[2]);
-      stv<T>(buf + (size_t)qb[u] * qs + pidx(d, y[u][0], y[u][1], kk), val);
-      const double fq = vq + wq, fb = val + wq;
-      for (int a = 0; a < 3; ++a) Fq[a] = (c[a] - ub[a]) * fq - (-c[a] - ub[a]) * fb;
-    } else {
-      for (int a = 0; a < 3; ++a) Fq[a] = 2.0 * wq * c[a];
-      arm[0] = min_image(((double)y[u][0] + 0.5) - xp[0], d.nx, d.walls[0]) - 0.5 * c[0];
-      arm[1] = min_image(((double)y[u][1] + 0.5) - xp[1], d.ny, d.walls[1]) - 0.5 * c[1];
-      arm[2] = min_image(((double)kk + 0.5) - xp[2], d.nz, d.walls[2]) - 0.5 * c[2];
-    }
-    acc[0] += Fq[0];
-    acc[1] += Fq[1];
-    acc[2] += Fq[2];
-    acc[3] += arm[1] * Fq[2] - arm[2] * Fq[1];
-    acc[4] += arm[2] * Fq[0] - arm[0] * Fq[2];
-    acc[5] += arm[0] * Fq[1] - arm[1] * Fq[0];
-  }
+  acc[0] += Fq[0];
+  acc[1] += Fq[1];
+  acc[2] += Fq[2];
+  acc[3] += arm[1] * Fq[2] - arm[2] * Fq[1];
+  acc[4] += arm[2] * Fq[0] - arm[0] * Fq[2];
+  acc[5] += arm[0] * Fq[1] - arm[1] * Fq[0];
 }
 
+constexpr int STAGE_UNROLL = 8;
+
+// Boundary pass of one block (sphere i, slabs bz, bz + ZB, ..., row chunks
+// brow, brow + rowb, ...): the states of the chunk's cells and of a 2-cell
+// halo (the CLI needs x - c_q of the fluid cell x = y - c_q) are staged in
+// LDS, so that link detection needs no dependent global loads; then flags and
+// owners are written and the links formed.  Bound by the chain of a block (its
+// sphere, the states, the links' populations, the reduction), one after the
+// other, and by how many blocks a CU holds: four at 128 VGPRs (two at the 186
+// that two links in flight and a path around the staging took), with LDS for
+// the states of the chunk and not of the largest box.
 template <typename T>
 __device__ __forceinline__ void commit_block(const DevDomain& d, int blk, int cur, uint32_t stamp) {
   T* buf = (T*)d.pdf[cur];
-  const int nbs = d.ZB * d.RB;
+  const int nbs = d.ZB * d.rowb;
   const int i = blk / nbs, b = blk % nbs;
-  const int bz = b / d.RB, brow = b % d.RB;
+  const int bz = b / d.rowb, brow = b % d.rowb;
   Box bx;
   sphere_box(d, i, true, bx);
   const double xp[3] = {d.p.x[3 * i], d.p.x[3 * i + 1], d.p.x[3 * i + 2]};
@@ -746,134 +710,118 @@ __device__ __forceinline__ void commit_block(const DevDomain& d, int blk, int cu
     R2 = R * R;
     rs2 = rs * rs;
   }
-  // States of the slab's cells and of a 2-cell halo (the CLI needs x - c_q of
-  // the fluid cell x = y - c_q) are staged in LDS, so link detection needs no
-  // dependent global loads; boxes too large for LDS take the global path.
-  // A block works on row chunks of COMMIT_ROWS rows of the box slabs
-  // (slab bz, bz + ZB, ...; chunk brow, brow + RB, ...).
-  const int EX = bx.ext[0], EY = bx.ext[1], HX = EX + 4, HY = COMMIT_ROWS + 4;
-  const bool staged = HX * HY * 5 <= STAGE_BYTES;
-  __shared__ uint8_t st[STAGE_BYTES];
-  __shared__ uint32_t lk[(Q - 1) * 256];  // one chunk's links (at most 18 per cell)
+  extern __shared__ uint8_t st[];
+  __shared__ uint32_t lk[(Q - 1) * 256];  // one pass's links (at most 18 per cell)
   __shared__ int wsum[4];
+  __shared__ uint32_t qtab[Q];  // entry of direction q without its cell
+  if (threadIdx.x < Q) qtab[threadIdx.x] = link_entry(0, (int)threadIdx.x);
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int EX = bx.ext[0], EY = bx.ext[1];
+  const int cols = min(EX, d.cols);
   double acc[6] = {0, 0, 0, 0, 0, 0};
   for (int sl = bz; sl < bx.ext[2]; sl += d.ZB) {
     const int kz = bx.lo[2] + sl;
     const int kk = d.walls[2] ? kz : wrap_near(kz, d.nz);
-    // does this plane cut the new solid ball of sphere i?
+    // a plane that does not cut the new solid ball of sphere i has no links:
+    // only its own states are needed
     const double dzc = min_image(((double)kk + 0.5) - xp[2], d.nz, d.walls[2]);
     const bool cuts = dzc * dzc <= R2;
-    for (int ry0 = brow * COMMIT_ROWS; ry0 < EY; ry0 += d.RB * COMMIT_ROWS) {
-      const int nrow = min(COMMIT_ROWS, EY - ry0);
-      if (staged && cuts) {
+    for (int ry0 = brow * d.rows; ry0 < EY; ry0 += d.rowb * d.rows)
+      for (int cx0 = 0; cx0 < EX; cx0 += cols) {
+        const int nrow = min(d.rows, EY - ry0), ncol = min(cols, EX - cx0);
+        const int HX = ncol + 4, HY = nrow + 4;
+        const int o[3] = {bx.lo[0] + cx0 - 2, bx.lo[1] + ry0 - 2, kz - 2};
         __syncthreads();
-        // eight entries per thread and pass (one pass for boxes up to ~40
-        // cells wide), all loads issued before any use
-        const int NS = HX * HY * 5;
-        for (int t0 = threadIdx.x; t0 < NS; t0 += 8 * blockDim.x) {
-          bool in[8];
-          uint8_t fl[8];
-          unsigned long long kc[8];
-          uint32_t ss[8];
+        {
+          // one x position per thread, STAGE_UNROLL rows per pass, all loads
+          // issued before any use
+          const int step = (int)blockDim.x / HX;  // HX <= 256
+          const int hx = (int)threadIdx.x % HX, r1 = (cuts ? 5 : 3) * HY;
+          const int gx = o[0] + hx;
+          const bool inx = !d.walls[0] || (gx >= 0 && gx < d.nx);
+          const int ix = d.walls[0] ? gx : wrap_near(gx, d.nx);
+          int r = (cuts ? 0 : 2) * HY + (int)threadIdx.x / HX;
+          if ((int)threadIdx.x >= step * HX) r = r1;
+          for (; r < r1; r += STAGE_UNROLL * step) {
+            uint8_t fl[STAGE_UNROLL];
+            unsigned long long kc[STAGE_UNROLL];
+            uint32_t ss[STAGE_UNROLL];
 #pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            const int t = t0 + u * blockDim.x;
-            const int hx = t % HX, r = t / HX, hy = r % HY, hz = r / HY;
-            const int gx = bx.lo[0] - 2 + hx, gy = bx.lo[1] + ry0 - 2 + hy, gz = kz - 2 + hz;
-            in[u] = t < NS && (!d.walls[0] || (gx >= 0 && gx < d.nx)) &&
-                    (!d.walls[1] || (gy >= 0 && gy < d.ny)) && (!d.walls[2] || (gz >= 0 && gz < d.nz));
-            if (in[u]) {
-              const long long c = cidx(d, wrap_near(gx, d.nx), wrap_near(gy, d.ny), wrap_near(gz, d.nz));
-              fl[u] = d.flags[c];
-              kc[u] = d.claim[c];
-              ss[u] = d.shellstamp[c];
-            }
-          }
-#pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            const int t = t0 + u * blockDim.x;
-            if (t >= NS) continue;
-            uint8_t code = L_WALL;
-            if (in[u] && !(fl[u] & F_WALL)) {
-              if ((uint32_t)(kc[u] >> 32) == stamp) {
-                const int o = (int)(0xFFFFFFFFu - (uint32_t)(kc[u] & 0xFFFFFFFFull));
-                code = o == i ? L_OWN : L_OTHER;
-              } else {
-                code = ss[u] == stamp ? L_SHELL : L_FLUID;
+            for (int u = 0; u < STAGE_UNROLL; ++u) {
+              const int ru = r + u * step, hz = ru / HY, hy = ru - hz * HY;
+              const int gy = o[1] + hy, gz = o[2] + hz;
+              fl[u] = F_WALL;
+              if (ru < r1 && inx && (!d.walls[1] || (gy >= 0 && gy < d.ny)) &&
+                  (!d.walls[2] || (gz >= 0 && gz < d.nz))) {
+                const long long c = cidx(d, ix, wrap_near(gy, d.ny), wrap_near(gz, d.nz));
+                fl[u] = d.flags[c];
+                kc[u] = d.claim[c];
+                ss[u] = d.shellstamp[c];
               }
             }
-            st[t] = code;
+#pragma unroll
+            for (int u = 0; u < STAGE_UNROLL; ++u) {
+              const int ru = r + u * step;
+              if (ru >= r1) continue;
+              uint8_t code = L_WALL;
+              if (!(fl[u] & F_WALL)) {
+                if ((uint32_t)(kc[u] >> 32) == stamp)
+                  code = 0xFFFFFFFFu - (uint32_t)(kc[u] & 0xFFFFFFFFull) == (uint32_t)i ? L_OWN : L_OTHER;
+                else
+                  code = ss[u] == stamp ? L_SHELL : L_FLUID;
+              }
+              st[hx + HX * ru] = code;
+            }
           }
         }
         __syncthreads();
-      }
-      const int ncell = EX * nrow;
-      // the cell's state: staged when its plane cuts the solid ball (then
-      // only another sphere's solid needs the claim for its owner)
-      const bool stg = staged && cuts;
-      for (int t0 = 0; t0 < ncell; t0 += blockDim.x) {
-        const int t = t0 + threadIdx.x;
-        uint32_t mask = 0u;
-        if (t < ncell) {
-          const int tx = t % EX, ty = t / EX;
-          const int ii = d.walls[0] ? bx.lo[0] + tx : wrap_near(bx.lo[0] + tx, d.nx);
-          const int jj = d.walls[1] ? bx.lo[1] + ry0 + ty : wrap_near(bx.lo[1] + ry0 + ty, d.ny);
-          // only cells within the old or new shell ball of i can change through i
-          if (cell_d2(d, ii, jj, kk, xp) <= rs2 || cell_d2(d, ii, jj, kk, xo) <= rs2) {
-            const long long yc = cidx(d, ii, jj, kk);
-            const int cidx0 = (tx + 2) + HX * ((ty + 2) + HY * 2);
-            const int sc = stg ? (int)st[cidx0] : -1;
-            int own = -1, ns;
-            if (sc == L_OWN) {
-              ns = S_SOLID;
-              own = i;
-            } else if (sc == L_SHELL || sc == L_FLUID) {
-              ns = sc == L_SHELL ? S_SHELL : S_FLUID;
-            } else if (sc == L_WALL) {
-              ns = S_WALL;
-            } else {
-              ns = new_state(d, yc, stamp, &own);
-            }
-            if (ns != S_WALL) {
-              d.flags[yc] = ns == S_SOLID ? F_SOLID : (ns == S_SHELL ? F_SHELL : (uint8_t)0);
-              if (ns == S_SOLID) d.owner[yc] = own;
-            }
-            if (ns == S_SOLID && own == i) {
-              // the links of y: directions whose y - c_q is not this sphere's solid
+        const int ncell = ncol * nrow;
+        for (int t0 = 0; t0 < ncell; t0 += blockDim.x) {
+          const int t = t0 + threadIdx.x;
+          uint32_t mask = 0u;
+          int h = 0;
+          if (t < ncell) {
+            const int ty = t / ncol, tx = t - ty * ncol;
+            const int gx = o[0] + 2 + tx, gy = o[1] + 2 + ty;
+            const int ii = d.walls[0] ? gx : wrap_near(gx, d.nx), jj = d.walls[1] ? gy : wrap_near(gy, d.ny);
+            h = (tx + 2) + HX * ((ty + 2) + HY * 2);
+            const int sc = st[h];
+            // only cells within the old or new shell ball of i can change through i
+            if (sc != L_WALL && (cell_d2(d, ii, jj, kk, xp) <= rs2 || cell_d2(d, ii, jj, kk, xo) <= rs2)) {
+              const long long yc = cidx(d, ii, jj, kk);
+              const bool solid = sc == L_OWN || sc == L_OTHER;
+              d.flags[yc] = solid ? F_SOLID : (sc == L_SHELL ? F_SHELL : (uint8_t)0);
+              if (solid) d.owner[yc] = sc == L_OWN ? i : (int)(0xFFFFFFFFu - (uint32_t)(d.claim[yc] & 0xFFFFFFFFull));
+              if (sc == L_OWN) {
+                // the links of y: directions whose y - c_q is not this sphere's solid
 #pragma unroll
-              for (int q = 1; q < Q; ++q) {
-                const int c[3] = {CX[q], CY[q], CZ[q]};
-                const long long xg = stg ? 0 : cidx(d, wrapi(ii - c[0], d.nx), wrapi(jj - c[1], d.ny), wrapi(kk - c[2], d.nz));
-                if (slab_code(d, st, stg, cidx0, HX, HY, c, 1, xg, stamp, i) != L_OWN) mask |= 1u << q;
+                for (int q = 1; q < Q; ++q)
+                  if (st[h - (CX[q] + HX * (CY[q] + HY * CZ[q]))] != L_OWN) mask |= 1u << q;
               }
             }
           }
-        }
-        // ordered compaction of the chunk's links (cell order, then direction)
-        const int cnt = __popc(mask);
-        int v = cnt;
-        for (int o = 1; o < 64; o <<= 1) {
-          const int w = __shfl_up(v, o, 64);
-          if (lane >= o) v += w;
-        }
-        if (lane == 63) wsum[wid] = v;
-        __syncthreads();
-        int off = v - cnt, tot = 0;
-        for (int w = 0; w < nw; ++w) {
-          if (w < wid) off += wsum[w];
-          tot += wsum[w];
-        }
+          // ordered compaction of the pass's links (cell order, then direction)
+          const int cnt = __popc(mask);
+          int v = cnt;
 #pragma unroll
-        for (int q = 1; q < Q; ++q)
-          if (mask & (1u << q)) lk[off++] = link_entry(t, q);
-        __syncthreads();
-        for (int k0 = threadIdx.x; k0 < tot; k0 += LINK_UNROLL * blockDim.x)
-          slab_links<T, LINK_UNROLL>(d, buf, (size_t)d.nx, st, stg, lk, k0, tot, EX, HX, HY, bx.lo[0], bx.lo[1] + ry0, kk, i,
-                                     stamp, xp, up, wp, R, acc);
-        __syncthreads();  // the list, the wave sums and the staged states are reused
+          for (int s = 1; s < 64; s <<= 1) {
+            const int w = __shfl_up(v, s, 64);
+            if (lane >= s) v += w;
+          }
+          if (lane == 63) wsum[wid] = v;
+          __syncthreads();
+          int off = v - cnt, tot = 0;
+          for (int w = 0; w < nw; ++w) {
+            if (w < wid) off += wsum[w];
+            tot += wsum[w];
+          }
+          for (uint32_t m = mask; m; m &= m - 1u) lk[off++] = (uint32_t)h | qtab[__ffs(m) - 1];
+          __syncthreads();
+          for (int k = threadIdx.x; k < tot; k += blockDim.x)
+            sphere_link<T>(d, buf, st, lk[k], HX, HY, o, xp, up, wp, R, acc);
+          __syncthreads();  // the list and the wave sums are reused
+        }
       }
-    }
   }
   // fixed-order block reduction: wavefront shuffles, then across wavefronts
   __shared__ double red[6][8];
@@ -887,7 +835,10 @@ __device__ __forceinline__ void commit_block(const DevDomain& d, int blk, int cu
     double v = 0.0;
     const int nw = (blockDim.x + 63) >> 6;
     for (int w8 = 0; w8 < nw; ++w8) v += red[threadIdx.x][w8];
-    d.partial[((size_t)i * nbs + b) * 6 + threadIdx.x] = v;
+    // slots of row blocks that this launch does not have hold zero
+    double* out = d.partial + (size_t)(i * d.ZB + bz) * d.RB * 6 + threadIdx.x;
+    out[6 * brow] = v;
+    for (int k = brow + d.rowb; k < d.RB; k += d.rowb) out[6 * k] = 0.0;
   }
 }
 
@@ -912,7 +863,7 @@ __device__ __forceinline__ void last_block_advance(const DevDomain& d) {
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void k_commit(DevDomain d, int in_step, int advance) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_commit(DevDomain d, int in_step, int advance) {
   if (map_live(d.ctl, in_step)) commit_block<T>(d, blockIdx.x, map_buffer(d.ctl, in_step), map_stamp(d.ctl));
   if (advance) last_block_advance(d);
 }
@@ -942,94 +893,6 @@ __device__ __forceinline__ int mbin_index(const DevDomain& d, const double* x, i
 constexpr uint8_t L_UNSET = 5;  // cell outside the staged ball
 
 
-
-// Links k0, k0 + blockDim.x, ... (at most U of them below tot) of sphere i,
-// all loads issued before any is used.  y - c_q fluid: boundary value of
-// Eq. (MEM_CLI) into slot qbar of y (delta = 1/2 in the coefficients where
-// y - 2 c_q is not fluid), force of Eq. (MEM_Fq) and its torque about the
-// centre; y - c_q a wall or another sphere's solid: the missing-link force
-// 2 w_q c_q with the arm to the mid-point of the link.
-template <typename T, int U>
-__device__ __forceinline__ void ball_links(const DevDomain& d, T* buf, const uint8_t* st,
-                                           const uint32_t* lk, int k0, int tot, int he, const int* lo,
-                                           const double* xp, const double* up, const double* wp, double R,
-                                           double* acc) {
-  bool ok[U], cli[U];
-  int code[U], q[U], qb[U], cq[U][3], y[U][3];
-  T gq[U], gqb[U], gm[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int k = k0 + u * (int)blockDim.x;
-    ok[u] = k < tot;
-    const uint32_t e = ok[u] ? lk[k] : 0u;
-    const int t = (int)(e & 0xFFFFu);
-    q[u] = (int)((e >> 16) & 31u);
-    qb[u] = (int)((e >> 21) & 31u);
-    cq[u][0] = (int)((e >> 26) & 3u) - 1;
-    cq[u][1] = (int)((e >> 28) & 3u) - 1;
-    cq[u][2] = (int)((e >> 30) & 3u) - 1;
-    const int h[3] = {t % he, (t / he) % he, t / (he * he)};
-    y[u][0] = d.walls[0] ? lo[0] + h[0] : wrap_near(lo[0] + h[0], d.nx);
-    y[u][1] = d.walls[1] ? lo[1] + h[1] : wrap_near(lo[1] + h[1], d.ny);
-    y[u][2] = d.walls[2] ? lo[2] + h[2] : wrap_near(lo[2] + h[2], d.nz);
-    const int off = cq[u][0] + he * (cq[u][1] + he * cq[u][2]);
-    code[u] = ok[u] ? (int)st[t - off] : L_OWN;
-    cli[u] = false;
-    gq[u] = gqb[u] = gm[u] = (T)0.0f;
-    if (code[u] <= L_SHELL) {
-      // wall layers shield every non-wall cell, so y - c_q stays in range
-      const int xi = wrapi(y[u][0] - cq[u][0], d.nx), xj = wrapi(y[u][1] - cq[u][1], d.ny),
-                xk = wrapi(y[u][2] - cq[u][2], d.nz);
-      const size_t xg = pidx(d, xi, xj, xk);
-      gq[u] = buf[(size_t)q[u] * d.nx + xg];
-      gqb[u] = buf[(size_t)qb[u] * d.nx + xg];
-      if (d.boundary == 0 && st[t - 2 * off] <= L_SHELL) {
-        cli[u] = true;
-        gm[u] = buf[(size_t)q[u] * d.nx +
-                    pidx(d, wrapi(xi - cq[u][0], d.nx), wrapi(xj - cq[u][1], d.ny), wrapi(xk - cq[u][2], d.nz))];
-      }
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    if (!ok[u]) continue;
-    const int* c = cq[u];
-    const double wq = c[0] * c[0] + c[1] * c[1] + c[2] * c[2] == 1 ? 1.0 / 18 : 1.0 / 36;
-    double Fq[3], arm[3];
-    if (code[u] <= L_SHELL) {
-      const int xi = wrapi(y[u][0] - c[0], d.nx), xj = wrapi(y[u][1] - c[1], d.ny), xk = wrapi(y[u][2] - c[2], d.nz);
-      double r[3];
-      r[0] = min_image(((double)xi + 0.5) - xp[0], d.nx, d.walls[0]);
-      r[1] = min_image(((double)xj + 0.5) - xp[1], d.ny, d.walls[1]);
-      r[2] = min_image(((double)xk + 0.5) - xp[2], d.nz, d.walls[2]);
-      const double dl = link_delta(r, c, R);
-      for (int a = 0; a < 3; ++a) arm[a] = r[a] + dl * c[a];
-      double ub[3];
-      ub[0] = up[0] + (wp[1] * arm[2] - wp[2] * arm[1]);
-      ub[1] = up[1] + (wp[2] * arm[0] - wp[0] * arm[2]);
-      ub[2] = up[2] + (wp[0] * arm[1] - wp[1] * arm[0]);
-      const double dd = cli[u] ? dl : 0.5;
-      const double vq = raw_to_d<T>(gq[u]);
-      double val = vq;
-      if (cli[u]) val += (1.0 - 2.0 * dd) / (1.0 + 2.0 * dd) * (raw_to_d<T>(gm[u]) - raw_to_d<T>(gqb[u]));
-      val -= 4.0 / (1.0 + 2.0 * dd) * wq * 3.0 * (ub[0] * c[0] + ub[1] * c[1] + ub[2] * c[2]);
-      stv<T>(buf + (size_t)qb[u] * d.nx + pidx(d, y[u][0], y[u][1], y[u][2]), val);
-      const double fq = vq + wq, fb = val + wq;
-      for (int a = 0; a < 3; ++a) Fq[a] = (c[a] - ub[a]) * fq - (-c[a] - ub[a]) * fb;
-    } else {
-      for (int a = 0; a < 3; ++a) Fq[a] = 2.0 * wq * c[a];
-      arm[0] = min_image(((double)y[u][0] + 0.5) - xp[0], d.nx, d.walls[0]) - 0.5 * c[0];
-      arm[1] = min_image(((double)y[u][1] + 0.5) - xp[1], d.ny, d.walls[1]) - 0.5 * c[1];
-      arm[2] = min_image(((double)y[u][2] + 0.5) - xp[2], d.nz, d.walls[2]) - 0.5 * c[2];
-    }
-    acc[0] += Fq[0];
-    acc[1] += Fq[1];
-    acc[2] += Fq[2];
-    acc[3] += arm[1] * Fq[2] - arm[2] * Fq[1];
-    acc[4] += arm[2] * Fq[0] - arm[0] * Fq[2];
-    acc[5] += arm[0] * Fq[1] - arm[1] * Fq[0];
-  }
-}
 
 template <typename T>
 __device__ __forceinline__ void commit_ball(const DevDomain& d, int in_step, int i) {
@@ -1215,8 +1078,8 @@ __device__ __forceinline__ void commit_ball(const DevDomain& d, int in_step, int
       tot += all;
     }
     __syncthreads();
-    for (int k0 = threadIdx.x; k0 < tot; k0 += BALL_LINK_UNROLL * blockDim.x)
-      ball_links<T, BALL_LINK_UNROLL>(d, buf, st, lk, k0, tot, he, lo, xp, up, wp, R, acc);
+    for (int k = threadIdx.x; k < tot; k += blockDim.x)
+      sphere_link<T>(d, buf, st, lk[k], he, he, lo, xp, up, wp, R, acc);
     __syncthreads();  // the next chunk reuses the list and the wave sums
   }
   // 4. fixed-order block reduction
@@ -1667,13 +1530,13 @@ static void launch_update_t(const DevDomain& d, bool reconstruct, int in_step, i
   // The step control rides on the last block only where the launch has few
   // blocks: the count of finished blocks is one device-wide atomic per block,
   // which costs more than the saved launch once there are thousands.
-  const int blocks = d.map_ball ? xcd_grid(d.P) : nsb * d.RB;
+  const int blocks = d.map_ball ? xcd_grid(d.P) : nsb * d.rowb;
   const int fold = advance && blocks <= FOLD_ADVANCE_MAX_BLOCKS;
   if (d.map_ball) {
     hipLaunchKernelGGL(k_commit_ball<T>, dim3(blocks), dim3(BALL_THREADS), ball_lds_bytes(d.stage_edge, d.list_cap), s, d,
                        in_step, fold);
   } else {
-    hipLaunchKernelGGL(k_commit<T>, dim3(blocks), dim3(256), 0, s, d, in_step, fold);
+    hipLaunchKernelGGL(k_commit<T>, dim3(blocks), dim3(256), d.slab_bytes, s, d, in_step, fold);
   }
   if (advance && !fold) launch_advance(d, s);
 }
@@ -1720,7 +1583,7 @@ __global__ __launch_bounds__(256) void k_recon_batch(const DevDomain* __restrict
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void k_commit_batch(const DevDomain* __restrict__ tab, const int* __restrict__ start,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) void k_commit_batch(const DevDomain* __restrict__ tab, const int* __restrict__ start,
                                                       int ndom) {
   const int k = batch_domain(start, ndom, (int)blockIdx.x);
   const DevDomain& d = tab[k];
@@ -1738,7 +1601,7 @@ static void launch_update_batch_t(const BatchTables& b, hipStream_t s) {
   if (b.claim_blocks > 0)
     hipLaunchKernelGGL(k_recon_batch<T>, dim3(b.claim_blocks), dim3(256), 0, s, b.tab, b.claim_start, b.ndom);
   if (b.commit_blocks > 0)
-    hipLaunchKernelGGL(k_commit_batch<T>, dim3(b.commit_blocks), dim3(256), 0, s, b.tab, b.commit_start, b.ndom);
+    hipLaunchKernelGGL(k_commit_batch<T>, dim3(b.commit_blocks), dim3(256), b.slab_bytes, s, b.tab, b.commit_start, b.ndom);
 }
 
 void launch_update_batch(const BatchTables& b, hipStream_t s) {
