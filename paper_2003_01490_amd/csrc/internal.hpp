@@ -288,11 +288,11 @@ inline int xcd_grid(int tiles) { return (tiles + XCDS - 1) / XCDS * XCDS; }
 
 // LDS of a k_commit_ball block: the staged cube of cell codes (he^3 bytes),
 // the surface-cell list (16-bit cube indices) and one chunk's link list (up
-// to 18 links for each of BALL_THREADS cells, 32 bits each)
-constexpr int BALL_THREADS = 256;
-inline size_t ball_lds_bytes(int he, int list_cap) {
+// to 18 links for each of its threads' cells, 32 bits each)
+constexpr int BALL_THREADS = 256, BALL_THREADS_MAX = 512;
+inline size_t ball_lds_bytes(int he, int list_cap, int threads = BALL_THREADS) {
   return (((size_t)he * he * he + 15) & ~(size_t)15) + ((2 * (size_t)list_cap + 15) & ~(size_t)15) +
-         4 * (size_t)(Q - 1) * BALL_THREADS;
+         4 * (size_t)(Q - 1) * threads;
 }
 
 // domain of block b: the k with start[k] <= b < start[k+1] (binary search)

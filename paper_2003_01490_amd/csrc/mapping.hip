@@ -875,8 +875,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
 // sphere's solid cells that have a non-own neighbour are listed, and their
 // links are formed as in k_commit.  Dynamic LDS: edge^3 state bytes plus the
 // surface list.
-// threads per block of the in-step geometric kernels (one block per sphere)
-constexpr int GEO_THREADS = 64;
+// Threads per block of the in-step geometric kernels (one block per sphere).
+// They wait on chains of loads (bins, spheres, flags, neighbours), so few
+// spheres get wide blocks, which walk a ball's rows in one pass and rebuild
+// more cells at once; many fill the chip with one wavefront each.  Measured
+// (k_recon_geo + k_remap_geo, D = 12, us) with 64 / 256 / 512 threads: 156
+// spheres 75 / 55 / 43, 370 - / 61 / 57, 720 - / 71 / 85, 1250 171 / 99 / 123,
+// 2900 204 / 170 / 244, 10,000 424 / 477 / 791.
+constexpr int GEO_THREADS_MAX = 512;
+static int geo_threads(int P) { return P <= 512 ? GEO_THREADS_MAX : (P <= 4096 ? 256 : 64); }
 
 // mapping bin of a position
 __device__ __forceinline__ int mbin_index(const DevDomain& d, const double* x, int* b) {
@@ -904,7 +911,7 @@ __device__ __forceinline__ void commit_ball(const DevDomain& d, int in_step, int
   uint8_t* st = smem;
   uint16_t* list = reinterpret_cast<uint16_t*>(smem + ((NS + 15) & ~15));
   uint32_t* lk = reinterpret_cast<uint32_t*>(smem + ((NS + 15) & ~15) + ((2 * d.list_cap + 15) & ~15));
-  __shared__ double red[6][4];
+  __shared__ double red[6][BALL_THREADS_MAX / 64];
   const double xp[3] = {d.p.x[3 * i], d.p.x[3 * i + 1], d.p.x[3 * i + 2]};
   const double up[3] = {d.p.u[3 * i], d.p.u[3 * i + 1], d.p.u[3 * i + 2]};
   const double wp[3] = {d.p.w[3 * i], d.p.w[3 * i + 1], d.p.w[3 * i + 2]};
@@ -932,7 +939,7 @@ __device__ __forceinline__ void commit_ball(const DevDomain& d, int in_step, int
   // none), from the row's exact y and z offsets, widened by 1e-3.  Rows of a
   // cube that nearly spans a periodic x axis keep every cell.
   constexpr double EPS = 1e-3;
-  constexpr int CH = (Q - 1) * BALL_THREADS;
+  const int CH = (Q - 1) * (int)blockDim.x;
   uint32_t* chord = lk;
   const bool chorded = he * he <= CH && (d.walls[0] || he + 2 <= n[0]);
   if (chorded) {
@@ -1014,7 +1021,7 @@ __device__ __forceinline__ void commit_ball(const DevDomain& d, int in_step, int
   // central box of edge 2 ceil(R) + 3 can hold cells of this sphere (their
   // centres lie within R of x_p); its x-fastest order is the cube's.  The
   // wave counts alternate between two slots, so one barrier per pass does.
-  __shared__ int wcount[2][4];
+  __shared__ int wcount[2][BALL_THREADS_MAX / 64];
   int base = 0;
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
   const int rc = (int)ceil(R) + 1, E = 2 * rc + 1, h0 = H - rc;
@@ -1047,7 +1054,7 @@ __device__ __forceinline__ void commit_ball(const DevDomain& d, int in_step, int
   // cells of one PDF plane, so the uses of a line come close together
   double acc[6] = {0, 0, 0, 0, 0, 0};
   const int nl = base;  // the same in every thread
-  __shared__ int qcnt[Q][4];
+  __shared__ int qcnt[Q][BALL_THREADS_MAX / 64];
   for (int c0 = 0; c0 < nl; c0 += blockDim.x) {
     const int e = c0 + threadIdx.x;
     uint32_t mask = 0u;
@@ -1103,7 +1110,7 @@ __device__ __forceinline__ void commit_ball(const DevDomain& d, int in_step, int
 // 1.66 ms at 10,000 spheres, against 1.78 ms with four waves and two links
 // and ~1.9 ms with the three waves the unconstrained allocation allows
 template <typename T>
-__global__ __launch_bounds__(BALL_THREADS) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_commit_ball(DevDomain d,
+__global__ __launch_bounds__(BALL_THREADS_MAX) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_commit_ball(DevDomain d,
                                                                                              int in_step,
                                                                                              int advance) {
   const int t = xcd_tile((int)blockIdx.x, (int)gridDim.x);
@@ -1202,9 +1209,9 @@ __device__ inline int geo_state(const DevDomain& d, int i, int j, int k, int* ow
 // from the mapping bins around it: every cell of the box is then evaluated
 // against these few (about five at 16 % solids) instead of walking 27 bins per
 // cell, a chain of dependent loads per bin (24,000 moving spheres at 512^3:
-// k_recon_geo 587 -> 232 us, k_remap_geo 472 -> 197; 156 at 96^3 FP64 112 -> 43
-// and 85 -> 32).  A crowd that
-// exceeds the list falls back to the bins.
+// k_recon_geo 587 -> 232 us, k_remap_geo 472 -> 197; 156 at 96^3 FP64 with one
+// wavefront each 112 -> 43 and 85 -> 32).  A crowd that exceeds the list falls
+// back to the bins.
 constexpr int NEAR_MAX = 48;
 struct NearSet {
   int n;  // > NEAR_MAX: too many, use the bins
@@ -1303,7 +1310,7 @@ constexpr int GEO_LIST = 512;
 // the new positions, from neighbours fluid before (flags) and after
 // (geo_state); written into the buffer the sweep has just filled.
 template <typename T>
-__global__ __launch_bounds__(GEO_THREADS) void k_recon_geo(DevDomain d) {
+__global__ __launch_bounds__(GEO_THREADS_MAX) void k_recon_geo(DevDomain d) {
   if (!step_live(d.ctl)) return;
   const int i = blockIdx.x;
   if (i >= d.P) return;
@@ -1359,7 +1366,7 @@ __global__ __launch_bounds__(GEO_THREADS) void k_recon_geo(DevDomain d) {
 // Flags and owners inside a step (one block per sphere i): the cells of the
 // old and new shell boxes where i's solid or shell membership changed get the
 // state of the new positions.
-__global__ __launch_bounds__(GEO_THREADS) void k_remap_geo(DevDomain d) {
+__global__ __launch_bounds__(GEO_THREADS_MAX) void k_remap_geo(DevDomain d) {
   if (!step_live(d.ctl)) return;
   const int i = blockIdx.x;
   if (i >= d.P) return;
@@ -1485,12 +1492,12 @@ void launch_update_fused(const DevDomain& d, hipStream_t s) {
   if (d.P > 0) {
     hipLaunchKernelGGL(k_mbins, dim3(gp), dim3(256), 0, s, d, 1, 0);
     if (d.storage == 0)
-      hipLaunchKernelGGL(k_recon_geo<double>, dim3((unsigned)d.P), dim3(GEO_THREADS), 0, s, d);
+      hipLaunchKernelGGL(k_recon_geo<double>, dim3((unsigned)d.P), dim3(geo_threads(d.P)), 0, s, d);
     else if (d.storage == 1)
-      hipLaunchKernelGGL(k_recon_geo<float>, dim3((unsigned)d.P), dim3(GEO_THREADS), 0, s, d);
+      hipLaunchKernelGGL(k_recon_geo<float>, dim3((unsigned)d.P), dim3(geo_threads(d.P)), 0, s, d);
     else
-      hipLaunchKernelGGL(k_recon_geo<__half>, dim3((unsigned)d.P), dim3(GEO_THREADS), 0, s, d);
-    hipLaunchKernelGGL(k_remap_geo, dim3((unsigned)d.P), dim3(GEO_THREADS), 0, s, d);
+      hipLaunchKernelGGL(k_recon_geo<__half>, dim3((unsigned)d.P), dim3(geo_threads(d.P)), 0, s, d);
+    hipLaunchKernelGGL(k_remap_geo, dim3((unsigned)d.P), dim3(geo_threads(d.P)), 0, s, d);
   }
   hipLaunchKernelGGL(k_advance_fused, dim3(gp), dim3(256), 0, s, d);
 }
@@ -1510,6 +1517,14 @@ void launch_map_prepare(const DevDomain& d, bool lists, hipStream_t s) {
   if (d.P > 0) hipLaunchKernelGGL(k_mbins, dim3(gp), dim3(256), 0, s, d, 1, 0);
 }
 
+// Threads per block of the ball pass: wide blocks while every sphere's block is
+// resident at once, two per CU (156 spheres of D = 12 in FP64 78 -> 58 us; 720
+// take 115 us either way, 1250 161 us with 256 threads and 176 with 512).  By the
+// count alone: a sphere's sums must not depend on the LDS that max_radius takes
+// (at most 77 KB with 512 threads).
+constexpr int BALL_WIDE_MAX = 512;
+static int ball_threads(int P) { return P <= BALL_WIDE_MAX ? BALL_THREADS_MAX : BALL_THREADS; }
+
 template <typename T>
 static void launch_update_t(const DevDomain& d, bool reconstruct, int in_step, int advance, hipStream_t s) {
   const int nsb = d.P * d.ZB;
@@ -1521,8 +1536,8 @@ static void launch_update_t(const DevDomain& d, bool reconstruct, int in_step, i
     // inside a step: reconstruction and the flags and owners of the new
     // positions (outside, launch_mapping has updated them)
     if (in_step) {
-      if (reconstruct) hipLaunchKernelGGL(k_recon_geo<T>, dim3((unsigned)d.P), dim3(GEO_THREADS), 0, s, d);
-      hipLaunchKernelGGL(k_remap_geo, dim3((unsigned)d.P), dim3(GEO_THREADS), 0, s, d);
+      if (reconstruct) hipLaunchKernelGGL(k_recon_geo<T>, dim3((unsigned)d.P), dim3(geo_threads(d.P)), 0, s, d);
+      hipLaunchKernelGGL(k_remap_geo, dim3((unsigned)d.P), dim3(geo_threads(d.P)), 0, s, d);
     }
   } else if (reconstruct) {
     hipLaunchKernelGGL(k_recon<T>, dim3(nsb), dim3(256), 0, s, d, in_step);
@@ -1533,7 +1548,8 @@ static void launch_update_t(const DevDomain& d, bool reconstruct, int in_step, i
   const int blocks = d.map_ball ? xcd_grid(d.P) : nsb * d.rowb;
   const int fold = advance && blocks <= FOLD_ADVANCE_MAX_BLOCKS;
   if (d.map_ball) {
-    hipLaunchKernelGGL(k_commit_ball<T>, dim3(blocks), dim3(BALL_THREADS), ball_lds_bytes(d.stage_edge, d.list_cap), s, d,
+    const int nt = ball_threads(d.P);
+    hipLaunchKernelGGL(k_commit_ball<T>, dim3(blocks), dim3(nt), ball_lds_bytes(d.stage_edge, d.list_cap, nt), s, d,
                        in_step, fold);
   } else {
     hipLaunchKernelGGL(k_commit<T>, dim3(blocks), dim3(256), d.slab_bytes, s, d, in_step, fold);
