@@ -880,10 +880,11 @@ __global__ __launch_bounds__(DEM_LDS_THREADS) void k_dem_batch(const DevDomain* 
 }
 
 void launch_dem_batch(const BatchTables& b, hipStream_t s) {
+  // threads for the largest few-sphere domain there can be (domains with more
+  // spheres take any number)
   const int P = b.max_P < DEM_LDS_MAX ? b.max_P : DEM_LDS_MAX;
   if (b.ndom > 0 && b.max_P > 0)
-    hipLaunchKernelGGL(k_dem_batch, dim3(b.ndom), dim3(b.max_P > DEM_LDS_MAX ? 256u : dem_lds_threads(P)),
-                       dem_lds_bytes(P), s, b.tab, b.ndom);
+    hipLaunchKernelGGL(k_dem_batch, dim3(b.ndom), dim3(dem_lds_threads(P)), dem_lds_bytes(P), s, b.tab, b.ndom);
 }
 
 void launch_advance(const DevDomain& d, hipStream_t s) { hipLaunchKernelGGL(k_advance, dim3(1), dim3(1), 0, s, d); }

@@ -119,3 +119,28 @@ def test_geometric_mapping_in_a_crowd(count, n):
         check_all(sphere_errs(g.sphere(i), o.sphere(i), 5.0, {"u": 0.1, "F": F}),
                   fp64_bounds(**{k: BOUND for k in ("x", "u", "w", "F_fp", "F_raw", "F_tot", "F_lub", "F_col",
                                                     "T_fp", "T_raw")}), f"sphere {i}")
+
+
+@pytest.mark.parametrize("counts", [(1, 9), (40, 70), (64, 65)])
+def test_batch_of_few_and_many_spheres(counts):
+    """A batch whose domains lie on both sides of the few-sphere kernel's
+    limits: each the bits of the same domain alone (above the limit, of its
+    one-workgroup kernel)."""
+    import torch
+
+    from paper_2003_01490_amd import lbmdem as L
+
+    print(f"[case] batch of {counts} spheres", flush=True)
+    stream = torch.cuda.Stream()
+    wls = [W.dense(c, n=40, count=c, D=6.0, min_gap=0.1, u_rms=0.08, nu=0.02) for c in counts]
+    alone, mixed = [[gpu_domain(w, storage=1, stream=stream, map_kernel=1, dem_kernel=1) for w in wls] for _ in range(2)]
+    b = L.Batch(stream, pool_bytes=1 << 40)
+    for g in mixed:
+        b.admit(g)
+    b.step(12)
+    for a, m in zip(alone, mixed):
+        a.step(12)
+        sa, sm = a.spheres(), m.spheres()
+        assert all(np.array_equal(sa[k], sm[k]) for k in sa)
+        assert np.array_equal(a.field("pdf"), m.field("pdf"))
+    b.close()
