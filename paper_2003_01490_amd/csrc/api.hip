@@ -635,8 +635,10 @@ int32_t lbmdem_create(const lbmdem_config* cfg, void* dev_buf, size_t dev_bytes,
   d.status = (int*)(base + L.status);
   d.n_sub = cfg->n_sub;
   d.force_averaging = cfg->force_averaging;
-  d.e_dry = cfg->e_dry;
-  d.poisson_ratio = cfg->poisson_ratio;
+  d.log_e = std::log(cfg->e_dry);
+  d.kappa = 2.0 * (1.0 - cfg->poisson_ratio) / (2.0 - cfg->poisson_ratio);
+  d.sqrt_kappa = std::sqrt(d.kappa);
+  d.inv_cut_n = 1.0 / cfg->cut_n;
   d.friction = cfg->friction;
   d.tc = cfg->tc;
   d.dmin = cfg->dmin;

@@ -139,13 +139,14 @@ __device__ __forceinline__ void lubrication(const DevDomain& d, double dmin, con
     ut[a] = uij[a] - un[a];
   }
   const double k = wall ? 0.0 : Rj / Ri;
+  double L = 0.0;
   if ((d.lub_mask & 1) && delta > 0.0 && delta < d.cut_n) {
     const double coef = wall ? 1.0 : (k * k) / ((1.0 + k) * (1.0 + k));
-    const double mag = -6.0 * PI_D * mu * Ri * Ri * coef * (1.0 / dl - 1.0 / d.cut_n);
+    const double mag = -6.0 * PI_D * mu * Ri * Ri * coef * (1.0 / dl - d.inv_cut_n);
     for (int a = 0; a < 3; ++a) F[a] += mag * un[a];
   }
   if ((d.lub_mask & 2) && delta > 0.0 && delta < d.cut_tt) {
-    const double L = log(dl / d.cut_tt);
+    L = log(dl / d.cut_tt);
     const double cf = wall ? 8.0 / 15.0
                            : 4.0 * k * (2.0 + k + 2.0 * k * k) / (15.0 * (1.0 + k) * (1.0 + k) * (1.0 + k));
     const double ct = wall ? 0.1 : k * (4.0 + k) / (10.0 * (1.0 + k) * (1.0 + k));
@@ -159,7 +160,7 @@ __device__ __forceinline__ void lubrication(const DevDomain& d, double dmin, con
     }
   }
   if ((d.lub_mask & 4) && delta > 0.0 && delta < d.cut_tr) {
-    const double L = log(dl / d.cut_tr);
+    if (!((d.lub_mask & 2) && d.cut_tr == d.cut_tt)) L = log(dl / d.cut_tr);  // else as above
     const double cf = wall ? 2.0 / 15.0 : 2.0 * k * k / (15.0 * (1.0 + k) * (1.0 + k));
     const double ct = wall ? 0.4 : 2.0 * k / (5.0 * (1.0 + k));
     double wv[3], av[3], wxn[3];
@@ -210,12 +211,11 @@ __device__ __forceinline__ bool pair_terms(const DevDomain& d, bool contact, con
     const double meff = is_wall ? mi : mi * mj / (mi + mj);
     const double D = is_wall ? 2.0 * Ri : Ri + Rj;
     const double Tc = collision_time(d, D);
-    const double le = log(d.e_dry);
+    const double le = d.log_e;
     const double kn = meff * (PI_D * PI_D + le * le) / (Tc * Tc);  // Eq. (normalDEMparameters)
     const double dn = -2.0 * meff * le / Tc;
-    const double kp = 2.0 * (1.0 - d.poisson_ratio) / (2.0 - d.poisson_ratio);
-    const double kt = kp * kn;  // Eq. (tangentialCollisionParameters)
-    const double dt = sqrt(kp) * dn;
+    const double kt = d.kappa * kn;  // Eq. (tangentialCollisionParameters)
+    const double dt = d.sqrt_kappa * dn;
     double Fn[3];
     for (int a = 0; a < 3; ++a) Fn[a] = -kn * pt.delta * pt.n[a] - dn * un[a];
     const double hn = dot3(hv, pt.n);
@@ -692,7 +692,8 @@ __global__ __launch_bounds__(256) void k_dem(DevDomain d) {
 // one thread per sphere with the whole state in memory arrays: 1 sphere 37 ->
 // 18 us alone and 93 -> 44 us beside the 128x128x256 FP32 sweep (where every
 // memory access of a sub-cycle costs microseconds: none is left in the quiet
-// path), 40 agitated spheres 253 -> 78 us, 16 requests of a batch 73 -> 27 us.
+// path), 40 agitated spheres 253 -> 78 us (72 since the pair terms' constants come
+// with the domain), 16 requests of a batch 73 -> 27 us.
 // LDS bytes of P spheres
 __host__ __device__ inline size_t dem_lds_bytes(int P) {
   return (size_t)P * (8 * (3 + 6 + 6 + 6 + 2 + 3 * HIST_SLOTS) + 4 * HIST_SLOTS + NBR_MAX);

@@ -157,7 +157,9 @@ struct DevDomain {
   int n_sub;
   int force_averaging;
   double gravity[3];
-  double e_dry, poisson_ratio, friction, tc, dmin, cut_n, cut_tt, cut_tr;
+  double friction, tc, dmin, cut_n, cut_tt, cut_tr;
+  // ln e_dry, kappa of Eq. (tangentialCollisionParameters), its root, 1 / cut_n
+  double log_e, kappa, sqrt_kappa, inv_cut_n;
   int lub_mask;
   double nu;
   double skin;     // neighbour-list skin
