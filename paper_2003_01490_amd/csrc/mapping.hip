@@ -842,7 +842,11 @@ __device__ __forceinline__ void commit_block(const DevDomain& d, int blk, int cu
   }
 }
 
-constexpr int FOLD_ADVANCE_MAX_BLOCKS = 512;
+// Blocks up to which the step control rides on the last block of the boundary
+// pass: the count of finished blocks is one device-wide release and atomic per
+// block.  Added time against a launch of its own (4 to 5 us): 54 blocks 0.9 us,
+// 120 1.3, 160 (of 512 threads) 6.5, 376 16, 720 15.
+constexpr int FOLD_ADVANCE_MAX_BLOCKS = 128;
 
 // With `advance`, the last block of the launch to finish runs the step
 // control (saving a launch at the end of the step): every block has read the
@@ -1542,9 +1546,6 @@ static void launch_update_t(const DevDomain& d, bool reconstruct, int in_step, i
   } else if (reconstruct) {
     hipLaunchKernelGGL(k_recon<T>, dim3(nsb), dim3(256), 0, s, d, in_step);
   }
-  // The step control rides on the last block only where the launch has few
-  // blocks: the count of finished blocks is one device-wide atomic per block,
-  // which costs more than the saved launch once there are thousands.
   const int blocks = d.map_ball ? xcd_grid(d.P) : nsb * d.rowb;
   const int fold = advance && blocks <= FOLD_ADVANCE_MAX_BLOCKS;
   if (d.map_ball) {
