@@ -18,8 +18,8 @@
 // - ball pass (many spheres; one block per sphere) and fused step: the
 //   spheres are filed in mapping bins, and each cell whose membership in a
 //   sphere's ball or shell changed gets the state of the new positions from
-//   the spheres of its 27 bins (k_recon_geo reconstructs, k_remap_geo
-//   rewrites flags, owners and cell words); only the cells near the ends of
+//   the few spheres near the block's box, gathered from the bins (k_recon_geo
+//   reconstructs, k_remap_geo rewrites flags, owners and cell words); only the cells near the ends of
 //   the balls' row chords are tested.  The ball pass then forms the links
 //   from the cell words.
 // Links: for each solid cell y of sphere i and each direction q whose cell
@@ -147,19 +147,6 @@ template <>
 __device__ inline void stv<float>(float* p, double v) { *p = (float)v; }
 template <>
 __device__ inline void stv<__half>(__half* p, double v) { *p = __float2half_rn((float)v); }
-
-// iterate the cells of a box: slabs of sphere-block b, threads over x-y
-#define FOR_BOX_CELLS(d, bx, b, ZB, ...)                                             \
-  for (int sl = (b); sl < (bx).ext[2]; sl += (ZB)) {                                 \
-    const int kk = (d).walls[2] ? (bx).lo[2] + sl : wrap_near((bx).lo[2] + sl, (d).nz); \
-    const int nxy_ = (bx).ext[0] * (bx).ext[1];                                      \
-    for (int t = threadIdx.x; t < nxy_; t += blockDim.x) {                           \
-      const int tx = t % (bx).ext[0], ty = t / (bx).ext[0];                          \
-      const int ii = (d).walls[0] ? (bx).lo[0] + tx : wrap_near((bx).lo[0] + tx, (d).nx); \
-      const int jj = (d).walls[1] ? (bx).lo[1] + ty : wrap_near((bx).lo[1] + ty, (d).ny); \
-      __VA_ARGS__                                                                    \
-    }                                                                                \
-  }
 
 // Claims of sphere i's solid cells with a stamped key; the largest key (this
 // stamp, lowest id) wins a cell inside several spheres.  With `lists` (the
@@ -872,13 +859,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
   if (advance) last_block_advance(d);
 }
 
-// Many spheres: one block per sphere.  The states of all cells within R + 3 of
-// the new centre (every cell a link of the sphere or its CLI neighbour can
-// touch) are staged in LDS in one pass with many loads in flight; then the
-// flags of the cells in the old and new shell balls are committed, the
-// sphere's solid cells that have a non-own neighbour are listed, and their
-// links are formed as in k_commit.  Dynamic LDS: edge^3 state bytes plus the
-// surface list.
 // Threads per block of the in-step geometric kernels (one block per sphere).
 // They wait on chains of loads (bins, spheres, flags, neighbours), so few
 // spheres get wide blocks, which walk a ball's rows in one pass and rebuild
@@ -905,6 +885,17 @@ constexpr uint8_t L_UNSET = 5;  // cell outside the staged ball
 
 
 
+// Many spheres: one block per sphere.  The states of all cells within R + 3 of
+// the new centre (every cell a link of the sphere or its CLI neighbour can
+// touch) are staged in LDS in one pass with many loads in flight; then the
+// sphere's solid cells that have a non-own neighbour are listed and their
+// links formed as in k_commit.  Dynamic LDS: edge^3 state bytes, the surface
+// list and the link list of one chunk.  Bound by the partial cache lines its
+// links touch (about 2,600 links on 3,000 lines per sphere of D = 12): the
+// same accesses without any arithmetic take 2.1 of its 2.3 ms at 24,000
+// spheres in 512^3 FP32, the 4-byte stores alone 1.45.  Boundary values kept
+// in per-tile lists for the sweep to put in (2.38 ms, the sweep 0.1 ms more)
+// and loads one link ahead (2.42) were no faster.
 template <typename T>
 __device__ __forceinline__ void commit_ball(const DevDomain& d, int in_step, int i) {
   const int cur = map_buffer(d.ctl, in_step);
@@ -1110,9 +1101,10 @@ __device__ __forceinline__ void commit_ball(const DevDomain& d, int in_step, int
 // one block per sphere, taken in the space-filling-curve order and spread over
 // the XCDs in contiguous runs, so that neighbouring spheres, whose staging
 // balls and links share cache lines, are served by the same L2.  At least
-// five waves per SIMD (at most 96 VGPRs, one link in flight per thread):
-// 1.66 ms at 10,000 spheres, against 1.78 ms with four waves and two links
-// and ~1.9 ms with the three waves the unconstrained allocation allows
+// five waves per SIMD (at most 96 VGPRs, one link in flight per thread): when
+// this was set, 1.66 ms at 10,000 spheres (1.0 to 1.1 ms now), against 1.78 ms
+// with four waves and two links and ~1.9 ms with the three waves the
+// unconstrained allocation allows
 template <typename T>
 __global__ __launch_bounds__(BALL_THREADS_MAX) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_commit_ball(DevDomain d,
                                                                                              int in_step,
