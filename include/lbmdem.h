@@ -105,10 +105,12 @@ typedef struct lbmdem_config {
   int32_t max_spheres;      /* capacity, sizes the device region                 */
   double max_radius;        /* largest sphere radius that will be added, <= 1000 */
   int32_t dem_kernel;       /* DEM sub-cycle kernel: 0 automatic (one workgroup up
-                               to 64 spheres, else the chain), 1 one workgroup
+                               to 64 spheres, else the chain, with an all-pairs
+                               search up to 256 spheres), 1 one workgroup
                                (all-pairs neighbour search), 2 a group of lanes
                                per sphere over a chain of launches (binned
-                               neighbour search); results are identical          */
+                               neighbour search, at most 15 spheres in a bin:
+                               LBMDEM_ECAPACITY beyond); results are identical   */
   int32_t map_kernel;       /* particle-link boundary pass: 0 automatic (one
                                block per sphere from 128 spheres when it fits),
                                1 several blocks per sphere (box slabs and row

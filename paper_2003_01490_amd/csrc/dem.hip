@@ -18,8 +18,8 @@
 // Few spheres: one workgroup, eight lanes per sphere, state in LDS, sub-cycles
 // separated by workgroup barriers (beyond DEM_LDS_MAX spheres, where it is asked
 // for explicitly, one thread per sphere on global memory).  Many spheres: eight
-// lanes per sphere over a chain of launches; neighbours are found through
-// uniform bins, and x, u, w alternate between two buffers every sub-cycle
+// lanes per sphere over a chain of launches; neighbours are found by all pairs
+// (up to DEM_PAIRS_MAX spheres) or through uniform bins, and x, u, w alternate between two buffers every sub-cycle
 // (positions are advanced into the other buffer, then forces read the new
 // positions and the old velocities and write the new velocities into the other
 // buffer), so each sub-cycle needs only two launches.  All give the same bits.
@@ -922,21 +922,32 @@ __device__ __forceinline__ void bin_insert(const DevDomain& d, const DevParticle
     atomicOr(d.status, ST_NBR_FULL);
 }
 
-// The neighbour test of dem_body over the candidates of the surrounding bins,
-// by 32 lanes per sphere: lane e takes the e-th of the 27 bins, so the bins'
-// counts and ids are read in two round trips instead of 27 one after the other
-// (10,000 spheres beside the 384^3 sweep: 253 -> 23 us).  The partners are collected in LDS in any order and then
-// written by rank (ids are distinct), so every kernel produces the same list.
+// The neighbour test of dem_body by 32 lanes per sphere.  With bins lane e takes
+// the e-th of the 27 around the sphere, so their counts and ids are read in two
+// round trips instead of 27 one after the other (10,000 spheres beside the 384^3
+// sweep: 253 -> 23 us); without, spheres e, e + 32, ...  The partners are collected
+// in LDS in any order and then written by rank (ids are distinct), so every
+// kernel produces the same list.
 constexpr int NBR_LANES = 32;
-__device__ __forceinline__ void binned_neighbours(const DevDomain& d, const DevParticles& p, int i, int* cand,
-                                                  int* ncand) {
+__device__ __forceinline__ void lane_neighbours(const DevDomain& d, const DevParticles& p, int i, bool bins, int* cand,
+                                                int* ncand) {
   const int e = threadIdx.x & (NBR_LANES - 1);
   const bool on = i < d.P;
   if (e == 0) *ncand = 0;
   __syncthreads();
+  const double range = list_range(d);
+  auto test = [&](int j) {
+    if (j == i || !(pair_gap(d, p, i, j) < range)) return;
+    const int at = atomicAdd(ncand, 1);
+    if (at < NBR_MAX)
+      cand[at] = j;
+    else
+      atomicOr(d.status, ST_NBR_FULL);
+  };
   const double* x = p.x + 3 * (on ? i : 0);
-  if (on && isfinite(x[0]) && isfinite(x[1]) && isfinite(x[2])) {
-    const double range = list_range(d);
+  if (on && !bins) {
+    for (int j = e; j < d.P; j += NBR_LANES) test(j);
+  } else if (on && isfinite(x[0]) && isfinite(x[1]) && isfinite(x[2])) {
     int b[3];
     bin_index(d, x, b);
     const int n0 = d.bins.n[0], n1 = d.bins.n[1], n2 = d.bins.n[2];
@@ -946,15 +957,7 @@ __device__ __forceinline__ void binned_neighbours(const DevDomain& d, const DevP
         axis_bin(b[1], n1, d.walls[1], e / a0 % a1, &ky) && axis_bin(b[2], n2, d.walls[2], e / (a0 * a1), &kz)) {
       const int* c = d.bins.cell + (size_t)(kx + n0 * (ky + n1 * kz)) * (1 + BIN_CAP);
       const int m = min(c[0], BIN_CAP);
-      for (int k = 0; k < m; ++k) {
-        const int j = c[1 + k];
-        if (j == i || !(pair_gap(d, p, i, j) < range)) continue;
-        const int at = atomicAdd(ncand, 1);
-        if (at < NBR_MAX)
-          cand[at] = j;
-        else
-          atomicOr(d.status, ST_NBR_FULL);
-      }
+      for (int k = 0; k < m; ++k) test(c[1 + k]);
     }
   }
   __syncthreads();
@@ -978,18 +981,18 @@ __device__ __forceinline__ void binned_neighbours(const DevDomain& d, const DevP
 // sweep on a second stream, where a cooperative grid could not be sure of
 // having all its blocks resident.  Per sphere the arithmetic and its order are
 // those of the one-workgroup kernels (identical bits).
-__global__ __launch_bounds__(DEM_GRID_THREADS) void k_demg_prologue(DevDomain d) {
+__global__ __launch_bounds__(DEM_GRID_THREADS) void k_demg_prologue(DevDomain d, int bins) {
   if (dem_stopped(d)) return;
   const int lane = threadIdx.x & 63;
   const int i = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
   if (i >= d.P) return;
   resolved_force(d, d.p, i, lane);
-  if (lane == 0) bin_insert(d, d.p, i);
+  if (bins && lane == 0) bin_insert(d, d.p, i);
 }
 
 // the same where each sphere has one partial (one block per sphere in the
 // boundary pass): lane g < 6 of its group takes component g
-__global__ __launch_bounds__(DEM_GRID_THREADS) void k_demg_prologue_one(DevDomain d) {
+__global__ __launch_bounds__(DEM_GRID_THREADS) void k_demg_prologue_one(DevDomain d, int bins) {
   if (dem_stopped(d)) return;
   const int g = threadIdx.x & (GROUP - 1);
   const int i = (int)((blockIdx.x * blockDim.x + threadIdx.x) / GROUP);
@@ -1008,16 +1011,16 @@ __global__ __launch_bounds__(DEM_GRID_THREADS) void k_demg_prologue_one(DevDomai
     }
   }
   if (g < 3) p.xmap[3 * i + g] = p.x[3 * i + g];
-  if (g == 7) bin_insert(d, p, i);
+  if (bins && g == 7) bin_insert(d, p, i);
   if (g == 0 && d.force_averaging) p.prev_valid[i] = 1;
 }
 
-__global__ __launch_bounds__(DEM_GRID_THREADS) void k_demg_neighbours(DevDomain d) {
+__global__ __launch_bounds__(DEM_GRID_THREADS) void k_demg_neighbours(DevDomain d, int bins) {
   if (dem_stopped(d)) return;
   constexpr int PER = DEM_GRID_THREADS / NBR_LANES;
   __shared__ int cand[PER][NBR_MAX], ncand[PER];
   const int s = threadIdx.x / NBR_LANES;
-  binned_neighbours(d, d.p, (int)blockIdx.x * PER + s, cand[s], &ncand[s]);
+  lane_neighbours(d, d.p, (int)blockIdx.x * PER + s, bins != 0, cand[s], &ncand[s]);
 }
 
 // state of sub-cycle `sub` (even: the first buffers), and the other buffer
@@ -1033,10 +1036,10 @@ __device__ __forceinline__ void subcycle_buffers(const DevParticles& p, int sub,
   *w1 = odd ? p.w : p.w2;
 }
 
-__global__ __launch_bounds__(DEM_GRID_THREADS) void k_demg_position(DevDomain d, int sub) {
+__global__ __launch_bounds__(DEM_GRID_THREADS) void k_demg_position(DevDomain d, int sub, int bins) {
   if (dem_stopped(d)) return;
   const int gtid = blockIdx.x * blockDim.x + threadIdx.x;
-  if (sub == 0) {  // the lists are built: clear the bins for the next step
+  if (bins && sub == 0) {  // the lists are built: clear the bins for the next step
     const int nbins = d.bins.n[0] * d.bins.n[1] * d.bins.n[2];
     for (int k = gtid; k < nbins; k += gridDim.x * blockDim.x) d.bins.cell[(size_t)k * (1 + BIN_CAP)] = 0;
   }
@@ -1133,19 +1136,23 @@ hipError_t launch_dem(const DevDomain& d, int kernel, bool no_release, hipStream
   }
   const unsigned T = DEM_GRID_THREADS;
   auto grid = [&](int lanes) { return dim3((unsigned)(((long long)d.P * lanes + T - 1) / T)); };
+  // Lists by all pairs up to DEM_PAIRS_MAX spheres: a bin holds BIN_CAP of them,
+  // which a cluster of few spheres in a wide lattice (bins grow until their number
+  // is a few per sphere), or of small ones beside a large max_radius, exceeds.
+  const int bins = kernel == 2 || d.P > DEM_PAIRS_MAX ? 1 : 0;
   if (d.ZB * d.RB == 1)
-    hipLaunchKernelGGL(k_demg_prologue_one, grid(GROUP), dim3(T), 0, s, d);
+    hipLaunchKernelGGL(k_demg_prologue_one, grid(GROUP), dim3(T), 0, s, d, bins);
   else
-    hipLaunchKernelGGL(k_demg_prologue, grid(64), dim3(T), 0, s, d);
-  hipLaunchKernelGGL(k_demg_neighbours, grid(NBR_LANES), dim3(T), 0, s, d);
+    hipLaunchKernelGGL(k_demg_prologue, grid(64), dim3(T), 0, s, d, bins);
+  hipLaunchKernelGGL(k_demg_neighbours, grid(NBR_LANES), dim3(T), 0, s, d, bins);
   // (its threads also clear the bins, a few each: with only the threads of 156
   // spheres that alone took 20 us)
-  const long long clear = ((long long)d.bins.n[0] * d.bins.n[1] * d.bins.n[2] + 4 * T - 1) / (4 * T);
-  hipLaunchKernelGGL(k_demg_position, dim3(std::max(grid(1).x, (unsigned)clear)), dim3(T), 0, s, d, 0);
+  const long long clear = bins ? ((long long)d.bins.n[0] * d.bins.n[1] * d.bins.n[2] + 4 * T - 1) / (4 * T) : 0;
+  hipLaunchKernelGGL(k_demg_position, dim3(std::max(grid(1).x, (unsigned)clear)), dim3(T), 0, s, d, 0, bins);
   for (int sub = 0; sub < d.n_sub; ++sub) {
     const int fuse = no_release && sub + 1 < d.n_sub ? 1 : 0;
     hipLaunchKernelGGL(k_demg_velocity, grid(GROUP), dim3(T), 0, s, d, sub, fuse);
-    if (!fuse && sub + 1 < d.n_sub) hipLaunchKernelGGL(k_demg_position, grid(1), dim3(T), 0, s, d, sub + 1);
+    if (!fuse && sub + 1 < d.n_sub) hipLaunchKernelGGL(k_demg_position, grid(1), dim3(T), 0, s, d, sub + 1, bins);
   }
   if (d.n_sub & 1) hipLaunchKernelGGL(k_demg_epilogue, grid(1), dim3(T), 0, s, d);
   return hipGetLastError();

@@ -378,7 +378,7 @@ void launch_update_and_advance(const DevDomain& d, hipStream_t s);
 // buffers, move the stamp and evaluate the stop rule
 void launch_advance(const DevDomain& d, hipStream_t s);
 void launch_advance_batch(const BatchTables& b, hipStream_t s);
-// DEM sub-cycles.  kernel: 0 automatic, 1 single workgroup, 2 one thread per
+// DEM sub-cycles.  kernel: 0 automatic, 1 single workgroup, 2 eight lanes per
 // sphere over a chain of launches (binned neighbour search).  no_release: no
 // sphere is in (or can leave) prescribed motion, which lets the chain merge
 // each sub-cycle's position update into the previous velocity launch.
@@ -392,6 +392,9 @@ constexpr int DEM_GRID_THREADS = 128;
 // 161 us in three rounds of 512 threads, the chain 107 us; 40 spheres 78 us
 // against about 100.
 constexpr int DEM_LDS_MAX = 64;
+// Automatic choice: the chain lists neighbours by all pairs up to this many
+// spheres (any arrangement, any radii), through bins beyond.
+constexpr int DEM_PAIRS_MAX = 256;
 // planes [first, first + count) of a whole-lattice field (N doubles each), and
 // the canonical flags or owners (either may be NULL), into device memory
 enum { FIELD_RHO, FIELD_VEL, FIELD_PDF, FIELD_PDF_RAW };
