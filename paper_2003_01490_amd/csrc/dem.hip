@@ -361,7 +361,9 @@ struct GroupState {
 // lubrication and of the contact force and torque into *lub and *col of lane
 // g; nbr(k): the k-th listed neighbour.  Every lane of the wavefront
 // calls it (`on`: the group has a sphere).  hid: the sphere's 24 history codes;
-// hd: its springs.
+// hd: its springs.  A round's ended contacts free their slots and its new ones
+// take the first free slot one after the other in list order, as eval_forces
+// does: which slot, and whether there is one, is the same in every kernel.
 template <typename NBR>
 __device__ __forceinline__ void group_forces(const DevDomain& d, const GroupState& s, int i, bool on, int nn,
                                              NBR nbr, int* hid, double* hd, bool contact, bool upd, double dtp,
@@ -369,21 +371,23 @@ __device__ __forceinline__ void group_forces(const DevDomain& d, const GroupStat
   const int lane = threadIdx.x & 63, g = lane & (GROUP - 1), base = lane & ~(GROUP - 1);
   const double maxcut = longest_cut(d);
   double xi[3] = {0, 0, 0}, Ri = 0.0;
-  bool h = false;
   if (on) {
     for (int a = 0; a < 3; ++a) xi[a] = s.x[3 * i + a];
     Ri = s.R[i];
-#pragma unroll
-    for (int k = 0; k < HIST_SLOTS / GROUP; ++k) h = h || hid[g + GROUP * k] != INT_MIN;
   }
-  const bool any = ((__ballot(h) >> base) & 0xFFull) != 0;  // the sphere has a spring
+  unsigned mine = 0;  // bit k: slot g + 8 k is taken
+#pragma unroll
+  for (int k = 0; k < HIST_SLOTS / GROUP; ++k)
+    if (on && hid[g + GROUP * k] != INT_MIN) mine |= 1u << k;
+  const bool any = ((__ballot(mine != 0) >> base) & 0xFFull) != 0;  // the sphere has a spring
   const int nwalls = 2 * (d.walls[0] + d.walls[1] + d.walls[2]);
   const int tot = on ? nn + nwalls : 0;
   double sl = 0.0, sc = 0.0;
   for (int p0 = 0; __any(p0 < tot); p0 += GROUP) {
     const int pi = p0 + g;
-    double c[12] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-    bool reach = false;
+    double c[12] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}, hv[3] = {0, 0, 0};
+    bool reach = false, starts = false, ends = false;
+    int code = 0, slot = -1;
     if (pi < tot) {
       const bool wall = pi >= nn;
       int j = -1, a = 0, side = 0;
@@ -396,8 +400,7 @@ __device__ __forceinline__ void group_forces(const DevDomain& d, const GroupStat
         wall_of(d, pi - nn, &a, &side);
         delta = wall_gap(d, xi, Ri, a, side);
       }
-      const int code = wall ? -1 - (2 * a + side) : j;
-      int slot = -1;
+      code = wall ? -1 - (2 * a + side) : j;
       if (any)
         for (int q = 0; q < HIST_SLOTS; ++q)
           if (hid[q] == code) slot = q;
@@ -408,7 +411,7 @@ __device__ __forceinline__ void group_forces(const DevDomain& d, const GroupStat
           make_wall_partner(xi, Ri, a, side, delta, pt);
         else
           make_sphere_partner(xi, j, dd, dist, delta, pt);
-        double ui[3], wi[3], uj[3] = {0, 0, 0}, wj[3] = {0, 0, 0}, hv[3] = {0, 0, 0}, mj = 0.0;
+        double ui[3], wi[3], uj[3] = {0, 0, 0}, wj[3] = {0, 0, 0}, mj = 0.0;
         for (int q = 0; q < 3; ++q) {
           ui[q] = s.u[3 * i + q];
           wi[q] = s.w[3 * i + q];
@@ -423,18 +426,37 @@ __device__ __forceinline__ void group_forces(const DevDomain& d, const GroupStat
         if (slot >= 0)
           for (int q = 0; q < 3; ++q) hv[q] = hd[slot * 3 + q];
         const bool touch = pair_terms(d, contact, pt, xi, ui, wi, Ri, s.m[i], uj, wj, Rj, mj, dtp, hv, c);
-        if (upd && touch) {
-          // a free slot: lanes of a group may look for one at the same time
-          for (int q = 0; q < HIST_SLOTS && slot < 0; ++q)
-            if (atomicCAS(hid + q, INT_MIN, code) == INT_MIN) slot = q;
-          if (slot < 0) {
-            atomicOr(d.status, ST_HIST_FULL);
-          } else {
-            for (int q = 0; q < 3; ++q) hd[slot * 3 + q] = hv[q];
-          }
-        } else if (upd && slot >= 0) {
-          hid[slot] = INT_MIN;
+        starts = upd && touch && slot < 0;
+        ends = upd && !touch && slot >= 0;
+        if (upd && touch && slot >= 0)
+          for (int q = 0; q < 3; ++q) hd[slot * 3 + q] = hv[q];
+      }
+    }
+    if (__any(starts || ends)) {
+      const unsigned es = (unsigned)((__ballot(starts) >> base) & 0xFFull),
+                     ee = (unsigned)((__ballot(ends) >> base) & 0xFFull);
+      unsigned free_slots = 0;  // the same in the group's lanes
+      for (int k = 0; k < HIST_SLOTS / GROUP; ++k)
+        free_slots |= (unsigned)((__ballot(!((mine >> k) & 1u)) >> base) & 0xFFull) << (GROUP * k);
+#pragma unroll 1
+      for (int e = 0; e < GROUP; ++e) {
+        const int se = __shfl(slot, base + e, 64);
+        if ((ee >> e) & 1u) {
+          free_slots |= 1u << se;
+        } else if ((es >> e) & 1u) {
+          const int f = __ffs(free_slots) - 1;  // -1: none left
+          if (g == e) slot = f;
+          free_slots &= free_slots - 1u;
         }
+      }
+      mine = 0;
+      for (int k = 0; k < HIST_SLOTS / GROUP; ++k) mine |= (~free_slots >> (g + GROUP * k) & 1u) << k;
+      if (ends && ((free_slots >> slot) & 1u)) hid[slot] = INT_MIN;  // (not taken again)
+      if (starts && slot < 0) {
+        atomicOr(d.status, ST_HIST_FULL);
+      } else if (starts) {
+        hid[slot] = code;
+        for (int q = 0; q < 3; ++q) hd[slot * 3 + q] = hv[q];
       }
     }
     unsigned in = (unsigned)((__ballot(reach) >> base) & 0xFFull);
