@@ -1151,6 +1151,9 @@ int32_t lbmdem_get_field(lbmdem_domain* dom, int32_t field, void* dst, size_t by
   if (field == LBMDEM_FIELD_FLAGS || field == LBMDEM_FIELD_OWNER) {
     void* to = direct ? dst : (void*)stage;
     const bool flags = field == LBMDEM_FIELD_FLAGS;
+    // flags and owners arrive in the null stream's order, as a blocking copy's
+    // bytes do: after what the caller has enqueued there on the destination
+    if (direct && st) HIPCHK(dom, hipStreamSynchronize(nullptr));
     launch_get_map(dom->d, flags ? (uint8_t*)to : nullptr, flags ? nullptr : (int32_t*)to, st);
     HIPCHK(dom, hipGetLastError());
     if (!direct) HIPCHK(dom, hipMemcpyAsync(dst, stage, need, kind, st));
