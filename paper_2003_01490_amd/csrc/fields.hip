@@ -160,7 +160,9 @@ __global__ __launch_bounds__(256) void k_probe_density(DevDomain d, double* io, 
     for (int a = 0; a < 3; ++a) {
       const double s = io[3 * (size_t)k + a] - 0.5;
       const double fl = floor(s);
-      const int i0 = (int)fl, o = (c >> a) & 1;
+      // (the range is checked before the conversion: a coordinate beyond the
+      // integers must not wrap into it)
+      const int i0 = (int)fmin(fmax(fl, -2147483648.0), 2147483646.0), o = (c >> a) & 1;
       const double fr = s - fl;
       if (d.walls[a]) ok = ok && i0 >= 0 && i0 + 1 < nn[a];
       ijk[a] = d.walls[a] ? i0 + o : wrapmod(i0 + o, nn[a]);
