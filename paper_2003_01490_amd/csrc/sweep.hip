@@ -45,7 +45,8 @@ constexpr int SWEEP_MAX_THREADS = 512;
 // let the L2 join: 75 x 61 x 101 FP32 22 -> 17 us, 429 x 151 x 100 277 -> 204,
 // 150 x 130 x 140 FP64 198 -> 190, the batch above 1.59 -> 1.33 ms (aligned
 // rows lose: 384^3 1.54 -> 1.64 ms, 128x128x256 FP64 220 -> 243 us, 200^3 FP64
-// 453 -> 482 us).
+// 453 -> 482 us).  With a body force the same: aligned rows 128x128x256 FP64 246 ->
+// 220 us, 384^3 FP32 1.64 -> 1.50 ms with non-temporal stores.
 __host__ __device__ inline bool nt_stores(int nx, int size) { return nx * size % 64 == 0; }
 
 template <typename T, bool FORCED, bool NTLOAD, bool NTSTORE>
@@ -164,7 +165,9 @@ static void launch_sweep_t(const DevDomain& d, bool beside, hipStream_t s) {
   // against 223 us).
   constexpr bool nt = sizeof(T) == 8;
   const unsigned lds = beside ? residency_lds(bx * by, sizeof(T) == 2 ? 24 : 20) : 0u;
-  if (d.forced)
+  if (d.forced && lines)
+    hipLaunchKernelGGL((k_sweep<T, true, nt, true>), grid, block, lds, s, d, gx, gy, chunk);
+  else if (d.forced)
     hipLaunchKernelGGL((k_sweep<T, true, nt, false>), grid, block, lds, s, d, gx, gy, chunk);
   else if (lines)
     hipLaunchKernelGGL((k_sweep<T, false, nt, true>), grid, block, lds, s, d, gx, gy, chunk);
