@@ -564,7 +564,7 @@ int32_t lbmdem_create(const lbmdem_config* cfg, void* dev_buf, size_t dev_bytes,
     default: d.s_minus = snu; d.s_bulk_shell = snu; d.s_bulk_other = snu; break;
   }
   d.delta_ab = cfg->delta_ab;
-  sweep_tiles(d.nx, d.ny, d.storage, 256, &d.sw_bx, &d.sw_by, &d.sw_gx, &d.sw_gy);
+  sweep_tiles(d.nx, d.ny, d.storage, true, &d.sw_bx, &d.sw_by, &d.sw_gx, &d.sw_gy);
   d.pdf[0] = base + L.pdf0;
   d.pdf[1] = base + L.pdf1;
   d.flags = (uint8_t*)(base + L.flags);
@@ -1500,8 +1500,13 @@ static int32_t build_tables(lbmdem_batch* b) {
   b->t.sweep_blocks = ss[nd];
   b->t.claim_blocks = cs[nd];
   b->t.commit_blocks = ms[nd];
-  b->t.slab_bytes = 0;
-  for (const DevDomain& d : tab) b->t.slab_bytes = std::max(b->t.slab_bytes, d.slab_bytes);
+  b->t.slab_bytes = b->t.forced = 0;
+  b->t.sweep_threads = 256;
+  for (const DevDomain& d : tab) {
+    b->t.slab_bytes = std::max(b->t.slab_bytes, d.slab_bytes);
+    b->t.forced |= d.forced;
+    if (d.sw_bx * d.sw_by > 256) b->t.sweep_threads = 512;
+  }
   b->t.storage = b->storage;
   b->d_steps = (long long*)(m + tb + 3 * ib);
   b->d_stopped = (int*)(m + tb + 3 * ib + align256(8 * (size_t)std::max(nd, 1)));

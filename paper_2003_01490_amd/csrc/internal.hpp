@@ -274,7 +274,9 @@ struct BatchTables {
   const int* commit_start;  // P * ZB * rowb sphere blocks per domain
   int slab_bytes;           // largest of the domains'
   int ndom;
-  int max_P;  // most spheres in one domain
+  int max_P;   // most spheres in one domain
+  int forced;  // a domain has a body force
+  int sweep_threads;  // of a block: 512 if a domain sweeps rows of more than 256 cells whole, else 256
   int sweep_blocks, claim_blocks, commit_blocks;
   int storage;
 };
@@ -353,8 +355,8 @@ __device__ inline void step_control(const DevDomain& d) {
   advance_step(d, d.p);
 }
 
-// tiles of the sweep: bx x by cells (at most max_threads), gx x gy per z plane
-void sweep_tiles(int nx, int ny, int storage, int max_threads, int* bx, int* by, int* gx, int* gy);
+// tiles of the sweep: bx x by cells (at most 512), gx x gy per z plane
+void sweep_tiles(int nx, int ny, int storage, bool batch, int* bx, int* by, int* gx, int* gy);
 
 // host-side launchers (implemented in the .hip files)
 // beside: other kernels run beside it on a second stream

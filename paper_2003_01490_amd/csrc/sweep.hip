@@ -73,10 +73,14 @@ __global__ __launch_bounds__(SWEEP_MAX_THREADS) void k_sweep(DevDomain d, int gx
 // (or row pieces) as in the single sweep: tiles of 256 consecutive cells, cut
 // anywhere in a row, share the lines at both cuts of all 19 rows with another
 // block (16 requests of 48-192 cells a side, 31.8 M cells, FP32: 2.10 ms;
-// 1.52 ms with a plane of N cells per direction; whole rows 1.33 ms; more rows
-// per block 1.46 ms at 512 cells, 1.69 at 1024).
-template <typename T>
-__global__ __launch_bounds__(256) void k_sweep_batch(const DevDomain* __restrict__ tab,
+// 1.52 ms with a plane of N cells per direction; whole rows 1.35 ms; more rows
+// per block 1.46 ms at 512 cells, 1.69 at 1024).  The code of forced cells is
+// in a kernel of its own: beside it the unforced one takes 86 VGPRs instead of
+// 67 (steps of 8 domains: 150 x 130 x 140 FP32 732 -> 697 us, 130^3 626 -> 574,
+// 128^3 FP16 317 -> 303; 75 x 61 x 101 167 -> 172).  Forced cells are stored
+// plainly: 8 x 128^3 FP32 454 us a step, 463 with non-temporal stores.
+template <typename T, bool FORCED>
+__global__ __launch_bounds__(SWEEP_MAX_THREADS) void k_sweep_batch(const DevDomain* __restrict__ tab,
                                                      const int* __restrict__ start, int ndom) {
   using C = typename Store<T>::C;
   const int k = batch_domain(start, ndom, (int)blockIdx.x);
@@ -91,7 +95,7 @@ __global__ __launch_bounds__(256) void k_sweep_batch(const DevDomain* __restrict
   const T* src = (const T*)d.pdf[cur];
   T* dst = (T*)d.pdf[cur ^ 1];
   const C sp = (C)d.s_plus, sm = (C)d.s_minus, dbs = (C)(d.s_bulk_shell - d.s_plus), dbo = (C)(d.s_bulk_other - d.s_plus);
-  if (d.forced)  // uniform over the block (one domain)
+  if (FORCED && d.forced)  // uniform over the block (one domain)
     sweep_cell<T, true, false, false>(d, src, dst, x, y, z, sp, sm, dbs, dbo);
   else if (nt_stores(d.nx, (int)sizeof(T)))
     sweep_cell<T, false, false, true>(d, src, dst, x, y, z, sp, sm, dbs, dbo);
@@ -108,10 +112,13 @@ __global__ __launch_bounds__(256) void k_sweep_batch(const DevDomain* __restrict
 // 825 us against 890 in 160s; 256^3 FP64 128 x 2 0.89 ms against 0.90 whole.
 // Other rows share the line at each junction of their 19 rows, so they stay
 // whole up to 512 cells, 256 at FP64 (429 x 151 x 100: FP32 204 us against 222
-// in 215s; FP64 428 us in 215s against 474 whole).
-void sweep_tiles(int nx, int ny, int storage, int max_threads, int* bx, int* by, int* gx, int* gy) {
+// in 215s; FP64 428 us in 215s against 474 whole).  In a batch, whose blocks
+// all have the threads of the largest tile, the wide FP16 rows of whole pieces
+// stay in 128s (8 x 384 x 64 x 64: 248 us a step against 285 whole), the other
+// rows whole (8 x 300 x 100 x 90 FP32 675 us a step against 792 in 150s).
+void sweep_tiles(int nx, int ny, int storage, bool batch, int* bx, int* by, int* gx, int* gy) {
   const bool lines = nt_stores(nx, storage == 0 ? 8 : (storage == 1 ? 4 : 2));
-  const int whole = std::min(max_threads, lines ? (storage == 2 ? 512 : (storage == 1 ? 256 : 128)) : (storage == 0 ? 256 : 512));
+  const int whole = lines ? (storage == 2 ? (batch ? 256 : 512) : (storage == 1 ? 256 : 128)) : (storage == 0 ? 256 : 512);
   *bx = nx;
   if (nx > whole) {
     const int cand[4] = {128, 64, 160, 96};
@@ -147,7 +154,7 @@ static unsigned residency_lds(int threads, int waves) {
 template <typename T>
 static void launch_sweep_t(const DevDomain& d, bool beside, hipStream_t s) {
   int bx, by, gx, gy;
-  sweep_tiles(d.nx, d.ny, d.storage, SWEEP_MAX_THREADS, &bx, &by, &gx, &gy);
+  sweep_tiles(d.nx, d.ny, d.storage, false, &bx, &by, &gx, &gy);
   const dim3 block((unsigned)bx, (unsigned)by);
   const bool lines = nt_stores(d.nx, (int)sizeof(T));
   // Tile order: plain (x fastest), except for pieces of rows that share lines
@@ -186,7 +193,11 @@ void launch_sweep(const DevDomain& d, bool beside, hipStream_t s) {
 
 template <typename T>
 static void launch_sweep_batch_t(const BatchTables& b, hipStream_t s) {
-  hipLaunchKernelGGL(k_sweep_batch<T>, dim3(b.sweep_blocks), dim3(256), 0, s, b.tab, b.sweep_start, b.ndom);
+  const dim3 grid(b.sweep_blocks), block(b.sweep_threads);
+  if (b.forced)
+    hipLaunchKernelGGL((k_sweep_batch<T, true>), grid, block, 0, s, b.tab, b.sweep_start, b.ndom);
+  else
+    hipLaunchKernelGGL((k_sweep_batch<T, false>), grid, block, 0, s, b.tab, b.sweep_start, b.ndom);
 }
 
 void launch_sweep_batch(const BatchTables& b, hipStream_t s) {
