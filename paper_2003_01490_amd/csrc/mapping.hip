@@ -674,9 +674,9 @@ constexpr int STAGE_UNROLL = 8;
 // LDS, so that link detection needs no dependent global loads; then flags and
 // owners are written and the links formed.  Bound by the chain of a block (its
 // sphere, the states, the links' populations, the reduction), one after the
-// other, and by how many blocks a CU holds: four at 128 VGPRs (two at the 186
-// that two links in flight and a path around the staging took), with LDS for
-// the states of the chunk and not of the largest box.
+// other, and by how many blocks a CU holds: four at 128 VGPRs, 4 of them spilled
+// (two at the 186 that two links in flight and a path around the staging took),
+// with LDS for the states of the chunk and not of the largest box.
 template <typename T>
 __device__ __forceinline__ void commit_block(const DevDomain& d, int blk, int cur, uint32_t stamp) {
   T* buf = (T*)d.pdf[cur];
@@ -1582,18 +1582,25 @@ __global__ __launch_bounds__(256) void k_claim_batch(const DevDomain* __restrict
   claim_block(d, (int)blockIdx.x - start[k], map_stamp(d.ctl), false);
 }
 
+// Three waves per SIMD (168 VGPRs, 2 spilled; 178 unconstrained leave two): 8
+// domains with 30 spheres 39.9 -> 31.1 us, with 100 in FP64 100 -> 75 (four waves
+// 39.4 and 92, 35 spilled).
 template <typename T>
-__global__ __launch_bounds__(256) void k_recon_batch(const DevDomain* __restrict__ tab, const int* __restrict__ start,
-                                                     int ndom) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) void k_recon_batch(
+    const DevDomain* __restrict__ tab, const int* __restrict__ start, int ndom) {
   const int k = batch_domain(start, ndom, (int)blockIdx.x);
   const DevDomain& d = tab[k];
   if (!step_live(d.ctl)) return;
   recon_block<T>(d, (int)blockIdx.x - start[k], map_buffer(d.ctl, 1), map_stamp(d.ctl));
 }
 
+// With the descriptor in memory the pass takes 220 VGPRs, two waves per SIMD; at
+// three it spills 43 of 168 (FP16: 2 of 168), at four 83 of 128.  Two / three /
+// four waves, us: 8 domains with one sphere 15.0 / 21.3 / 30.5, with 30 spheres 95 /
+// 109 / 148, with 100 in FP64 286 / 324 / 468; 32 with four in FP16 95 / 71 / 121.
 template <typename T>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) void k_commit_batch(const DevDomain* __restrict__ tab, const int* __restrict__ start,
-                                                      int ndom) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 ? 3 : 2, 8))) void k_commit_batch(
+    const DevDomain* __restrict__ tab, const int* __restrict__ start, int ndom) {
   const int k = batch_domain(start, ndom, (int)blockIdx.x);
   const DevDomain& d = tab[k];
   if (!step_live(d.ctl)) return;
