@@ -371,14 +371,13 @@ __device__ __forceinline__ void group_forces(const DevDomain& d, const GroupStat
   const int lane = threadIdx.x & 63, g = lane & (GROUP - 1), base = lane & ~(GROUP - 1);
   const double maxcut = longest_cut(d);
   double xi[3] = {0, 0, 0}, Ri = 0.0;
+  unsigned mine = 0;  // bit k: slot g + 8 k is taken
   if (on) {
     for (int a = 0; a < 3; ++a) xi[a] = s.x[3 * i + a];
     Ri = s.R[i];
-  }
-  unsigned mine = 0;  // bit k: slot g + 8 k is taken
 #pragma unroll
-  for (int k = 0; k < HIST_SLOTS / GROUP; ++k)
-    if (on && hid[g + GROUP * k] != INT_MIN) mine |= 1u << k;
+    for (int k = 0; k < HIST_SLOTS / GROUP; ++k) mine |= (unsigned)(hid[g + GROUP * k] != INT_MIN) << k;
+  }
   const bool any = ((__ballot(mine != 0) >> base) & 0xFFull) != 0;  // the sphere has a spring
   const int nwalls = 2 * (d.walls[0] + d.walls[1] + d.walls[2]);
   const int tot = on ? nn + nwalls : 0;
@@ -432,10 +431,13 @@ __device__ __forceinline__ void group_forces(const DevDomain& d, const GroupStat
           for (int q = 0; q < 3; ++q) hd[slot * 3 + q] = hv[q];
       }
     }
-    if (__any(starts || ends)) {
+    unsigned in = (unsigned)((__ballot(reach) >> base) & 0xFFull);
+    if (!__any(in != 0)) continue;
+    if (__builtin_expect(__any(starts || ends), 0)) {
       const unsigned es = (unsigned)((__ballot(starts) >> base) & 0xFFull),
                      ee = (unsigned)((__ballot(ends) >> base) & 0xFFull);
       unsigned free_slots = 0;  // the same in the group's lanes
+#pragma unroll 1
       for (int k = 0; k < HIST_SLOTS / GROUP; ++k)
         free_slots |= (unsigned)((__ballot(!((mine >> k) & 1u)) >> base) & 0xFFull) << (GROUP * k);
 #pragma unroll 1
@@ -450,6 +452,7 @@ __device__ __forceinline__ void group_forces(const DevDomain& d, const GroupStat
         }
       }
       mine = 0;
+#pragma unroll 1
       for (int k = 0; k < HIST_SLOTS / GROUP; ++k) mine |= (~free_slots >> (g + GROUP * k) & 1u) << k;
       if (ends && ((free_slots >> slot) & 1u)) hid[slot] = INT_MIN;  // (not taken again)
       if (starts && slot < 0) {
@@ -459,7 +462,6 @@ __device__ __forceinline__ void group_forces(const DevDomain& d, const GroupStat
         for (int q = 0; q < 3; ++q) hd[slot * 3 + q] = hv[q];
       }
     }
-    unsigned in = (unsigned)((__ballot(reach) >> base) & 0xFFull);
     while (__any(in != 0)) {
       const int src = in ? base + __ffs(in) - 1 : lane;
 #pragma unroll
