@@ -113,18 +113,21 @@ __global__ void k_set_plane(DevDomain d, int q, const double* src) {
     f[(size_t)q * d.nx + pidx_of(d, c)] = from_d<T>(src[c] - WQ[q]);
 }
 
-// one direction of a PDF buffer as a plain plane of N cells, as stored (out:
-// from the buffer into the plane, else back), for checkpoints
+// a PDF buffer as 19 plain planes of N cells, as stored (out: from the buffer
+// into the planes, else back), for checkpoints
 template <typename T>
-__global__ void k_plane_copy(DevDomain d, int buf, int q, T* plane, int out) {
-  T* f = (T*)d.pdf[buf];
-  for (size_t c = (size_t)blockIdx.x * blockDim.x + threadIdx.x; c < (size_t)d.N;
-       c += (size_t)gridDim.x * blockDim.x) {
-    const size_t p = (size_t)q * d.nx + pidx_of(d, c);
-    if (out)
-      plane[c] = f[p];
-    else
-      f[p] = plane[c];
+__global__ void k_planes_copy(DevDomain d, int buf, T* planes, int out) {
+  T* f = (T*)(buf ? d.pdf[1] : d.pdf[0]);
+  const size_t N = (size_t)d.N;
+  for (size_t c = (size_t)blockIdx.x * blockDim.x + threadIdx.x; c < N; c += (size_t)gridDim.x * blockDim.x) {
+    const size_t p = pidx_of(d, c);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      if (out)
+        planes[(size_t)q * N + c] = f[(size_t)q * d.nx + p];
+      else
+        f[(size_t)q * d.nx + p] = planes[(size_t)q * N + c];
+    }
   }
 }
 
@@ -279,13 +282,13 @@ void launch_set_pdf(const DevDomain& d, int q, const double* src, hipStream_t s)
     hipLaunchKernelGGL(k_set_plane<__half>, grid_for(d.N), dim3(256), 0, s, d, q, src);
 }
 
-void launch_plane_copy(const DevDomain& d, int buf, int q, void* plane, bool out, hipStream_t s) {
+void launch_planes_copy(const DevDomain& d, int buf, void* planes, bool out, hipStream_t s) {
   if (d.storage == 0)
-    hipLaunchKernelGGL(k_plane_copy<double>, grid_for(d.N), dim3(256), 0, s, d, buf, q, (double*)plane, out ? 1 : 0);
+    hipLaunchKernelGGL(k_planes_copy<double>, grid_for(d.N), dim3(256), 0, s, d, buf, (double*)planes, out ? 1 : 0);
   else if (d.storage == 1)
-    hipLaunchKernelGGL(k_plane_copy<float>, grid_for(d.N), dim3(256), 0, s, d, buf, q, (float*)plane, out ? 1 : 0);
+    hipLaunchKernelGGL(k_planes_copy<float>, grid_for(d.N), dim3(256), 0, s, d, buf, (float*)planes, out ? 1 : 0);
   else
-    hipLaunchKernelGGL(k_plane_copy<__half>, grid_for(d.N), dim3(256), 0, s, d, buf, q, (__half*)plane, out ? 1 : 0);
+    hipLaunchKernelGGL(k_planes_copy<__half>, grid_for(d.N), dim3(256), 0, s, d, buf, (__half*)planes, out ? 1 : 0);
 }
 
 void launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s) {

@@ -403,8 +403,8 @@ enum { FIELD_RHO, FIELD_VEL, FIELD_PDF, FIELD_PDF_RAW };
 void launch_fields(const DevDomain& d, int field, int first, int count, double* dst, hipStream_t s);
 void launch_get_map(const DevDomain& d, uint8_t* flags, int32_t* owner, hipStream_t s);
 void launch_set_pdf(const DevDomain& d, int q, const double* src, hipStream_t s);
-// direction q of PDF buffer buf to (out) or from a plane of N stored values
-void launch_plane_copy(const DevDomain& d, int buf, int q, void* plane, bool out, hipStream_t s);
+// PDF buffer buf to (out) or from 19 planes of N stored values
+void launch_planes_copy(const DevDomain& d, int buf, void* planes, bool out, hipStream_t s);
 // densities at n points: io holds 3n coordinates, then receives n results
 void launch_probe_density(const DevDomain& d, double* io, int n, hipStream_t s);
 void launch_fill_claims(const DevDomain& d, hipStream_t s);
