@@ -289,6 +289,13 @@ struct BatchTables {
 constexpr int XCDS = 8;
 __device__ __forceinline__ int xcd_tile(int w, int G) { return (w & (XCDS - 1)) * (G / XCDS) + w / XCDS; }
 inline int xcd_grid(int tiles) { return (tiles + XCDS - 1) / XCDS * XCDS; }
+// the same in shorter runs: of every 8 `run` tiles each XCD takes `run` in a row
+// (grid: a multiple of 8 run)
+__host__ __device__ inline int xcd_run_tile(int w, int run) {
+  const int g = w / (XCDS * run), r = w - g * (XCDS * run);
+  return g * (XCDS * run) + (r & (XCDS - 1)) * run + r / XCDS;
+}
+inline int xcd_run_grid(int tiles, int run) { return (tiles + XCDS * run - 1) / (XCDS * run) * (XCDS * run); }
 
 // LDS of a k_commit_ball block: the staged cube of cell codes (he^3 bytes),
 // the surface-cell list (16-bit cube indices) and one chunk's link list (up

@@ -33,9 +33,9 @@
 namespace lbmdem {
 
 // one domain: tiles of whole x-rows, or of row pieces on wide lattices (see
-// launch_sweep_t), gx x gy tiles per z plane, x fastest; with `chunk` each
-// XCD takes a contiguous run of tiles; the current buffer is read from the
-// domain's step state.  The 19 rows of a (y, z) lie next to each other, so a
+// sweep_tiles), gx x gy tiles per z plane, x fastest, handed to the XCDs in
+// runs (see launch_sweep_t; 1: tile by tile, 0: one run each); the current
+// buffer is read from the domain's step state.  The 19 rows of a (y, z) lie next to each other, so a
 // block stores one contiguous run: 512^3 FP32 3.51-3.53 ms alone (5.8 TB/s)
 // against 3.80 with a plane of N cells per direction.
 constexpr int SWEEP_MAX_THREADS = 512;
@@ -50,10 +50,10 @@ constexpr int SWEEP_MAX_THREADS = 512;
 __host__ __device__ inline bool nt_stores(int nx, int size) { return nx * size % 64 == 0; }
 
 template <typename T, bool FORCED, bool NTLOAD, bool NTSTORE>
-__global__ __launch_bounds__(SWEEP_MAX_THREADS) void k_sweep(DevDomain d, int gx, int gy, int chunk) {
+__global__ __launch_bounds__(SWEEP_MAX_THREADS) void k_sweep(DevDomain d, int gx, int gy, int run) {
   using C = typename Store<T>::C;
   if (!step_live(d.ctl)) return;
-  const int t = chunk ? xcd_tile((int)blockIdx.x, (int)gridDim.x) : (int)blockIdx.x;
+  const int t = run == 1 ? (int)blockIdx.x : (run ? xcd_run_tile((int)blockIdx.x, run) : xcd_tile((int)blockIdx.x, (int)gridDim.x));
   const int bx = t % gx, r = t / gx, by = r % gy, z = r / gy;
   if (z >= d.nz) return;
   const int cur = d.ctl->cur;
@@ -104,30 +104,46 @@ __global__ __launch_bounds__(SWEEP_MAX_THREADS) void k_sweep_batch(const DevDoma
 }
 
 // Tile shape.  Bounded by HBM bandwidth; what the shape changes is how many
-// tiles share cache lines.  Rows of whole 64-byte pieces: whole rows (256 / nx
-// of them) up to 256 cells, 512 at FP16, 128 at FP64; wider ones in pieces of
-// whole cache lines where the row has them: 384^3 FP32 128 x 2 1.49 ms against
-// 1.52 whole and 1.54 in 192s; 480 x 160 x 82 FP32 160 x 1 164 us against 166
-// whole, 175 in 256s and 186 in 240s, which end inside a line; 320^3 64 x 4
-// 825 us against 890 in 160s; 256^3 FP64 128 x 2 0.89 ms against 0.90 whole.
-// Other rows share the line at each junction of their 19 rows, so they stay
-// whole up to 512 cells, 256 at FP64 (429 x 151 x 100: FP32 204 us against 222
-// in 215s; FP64 428 us in 215s against 474 whole).  In a batch, whose blocks
-// all have the threads of the largest tile, the wide FP16 rows of whole pieces
-// stay in 128s (8 x 384 x 64 x 64: 248 us a step against 285 whole), the other
+// tiles share cache lines and which of its L2's channels an XCD uses.  Rows of
+// whole 64-byte pieces: whole rows (256 / nx of them) up to 256 cells, 512 at
+// FP16, 128 at FP64; wider ones in pieces (row_piece).  Other rows share the
+// line at each junction of their 19 rows, so they stay whole up to 512 cells, 256
+// at FP64 (429 x 151 x 100: FP32 204 us against 222 in 215s; FP64 428 us in 215s
+// against 474 whole), wider ones in equal pieces.  In a batch, whose blocks all
+// have the threads of the largest tile, the wide FP16 rows of whole pieces stay
+// in up to 256s (8 x 384 x 64 x 64: 248 us a step against 285 whole), the other
 // rows whole (8 x 300 x 100 x 90 FP32 675 us a step against 792 in 150s).
+//
+// Pieces of rows of whole 64-byte pieces: whole 128-byte lines, and either an odd
+// number of them or 1 KB each.  Tiles go to the eight XCDs one by one, so with an
+// even number an XCD keeps getting the same columns, and with short pieces only a
+// few channels of its L2.  GB/s, sweep alone: FP32 768 x 256 x 256 in six 128s 5,220, in
+// three 256s 5,640; 1024 x 256 x 256 in eight 128s 5,450, in five 224s 5,830, in four
+// 256s 5,940; 512 x 128 x 128 in four 128s 5,580, in three 192s 5,870, in two 256s 5,870; FP16
+// 1024 x 256 x 256 in eight 128s 5,010, in three 384s 6,000, in two 512s 5,920; FP64 512 x 128
+// x 128 in four 128s 5,790, in three 176s 5,760.  Pieces that end inside a line cost most:
+// equal parts of 182 to 253 cells of rows of 544 to 992 ran at 3,700 to 4,300, three or
+// five pieces of whole lines run at 5,550 to 5,940 (FP64 4,200 to 4,560 and 5,170 to 5,800,
+// FP16 3,760 to 4,080 and 5,270 to 5,550).  A row that an odd number of 128s, 64s, 160s or
+// 96s fills exactly is cut so (384^3 FP32 128 x 2, 320^3 64 x 4, 480 x 160 x 82 160 x 1: 1 %
+// above whole rows).
+static int row_piece(int nx, int size, int widest) {
+  const int line = 128 / size, cand[6] = {128, 64, 160, 96, 256, 512}, least = (nx + widest - 1) / widest;
+  for (int c : cand)
+    if (nx % c == 0 && c % line == 0 && c <= widest && (nx / c % 2 == 1 || c * size >= 1024)) return c;
+  if (least == 1) return nx;
+  auto piece = [&](int n) { return ((nx + n - 1) / n + line - 1) / line * line; };
+  for (int n = least | 1; n < least + 16; n += 2)
+    if (piece(n) <= widest && (nx + piece(n) - 1) / piece(n) % 2 == 1) return piece(n);
+  return piece(least);
+}
+
 void sweep_tiles(int nx, int ny, int storage, bool batch, int* bx, int* by, int* gx, int* gy) {
-  const bool lines = nt_stores(nx, storage == 0 ? 8 : (storage == 1 ? 4 : 2));
+  const int size = storage == 0 ? 8 : (storage == 1 ? 4 : 2);
+  const bool lines = nt_stores(nx, size);
   const int whole = lines ? (storage == 2 ? (batch ? 256 : 512) : (storage == 1 ? 256 : 128)) : (storage == 0 ? 256 : 512);
-  *bx = nx;
-  if (nx > whole) {
-    const int cand[4] = {128, 64, 160, 96};
-    *bx = 0;
-    for (int c : cand)
-      if (lines && !*bx && nx % c == 0) *bx = c;
-    const int widest = std::max(whole, 256), n = (nx + widest - 1) / widest;
-    if (!*bx) *bx = (nx + n - 1) / n;  // equal pieces
-  }
+  const int widest = std::max(whole, 256), n = (nx + widest - 1) / widest;
+  *bx = nx <= whole ? nx : (lines ? row_piece(nx, size, widest) : (nx + n - 1) / n);
   *by = *bx < 256 ? 256 / *bx : 1;
   *gx = (nx + *bx - 1) / *bx;
   *gy = (ny + *by - 1) / *by;
@@ -157,14 +173,22 @@ static void launch_sweep_t(const DevDomain& d, bool beside, hipStream_t s) {
   sweep_tiles(d.nx, d.ny, d.storage, false, &bx, &by, &gx, &gy);
   const dim3 block((unsigned)bx, (unsigned)by);
   const bool lines = nt_stores(d.nx, (int)sizeof(T));
-  // Tile order: plain (x fastest), except for pieces of rows that share lines
-  // or are a multiple of 512 cells, where contiguous runs of tiles per XCD are
-  // faster (512^3 FP32 3.53 against 3.91 ms, 1000 x 150 x 80 392 against 408
-  // us; elsewhere slower: 384^3 1.51 against 1.49 ms, 640 x 256 x 256 1.12
-  // against 1.07, 256^3 FP32 458 against 438 us, 128x128x256 117 against 110)
-  const int chunk = gx > 1 && (!lines || d.nx % 512 == 0) ? 1 : 0;
+  // Tile order: tile by tile over the XCDs, x fastest, except
+  // - pieces of rows that share lines: one contiguous run of tiles per XCD (1000 x
+  //   150 x 80 FP32 392 against 408 us);
+  // - FP32 and FP16 buffers of more than 2 GB: runs of 128 tiles, so that an XCD
+  //   touches fewer pages at a time, unless the row has five or more pieces of an odd
+  //   number.  GB/s tile by tile / in runs of 128 / in one run: FP32 512^3 (10 GB, two
+  //   256s) 5,640 / 5,880 / 5,830, 384^3 (4.3, three 128s) 5,680 / 5,840 / 5,670, 256 x 512 x
+  //   512 (5.1) 5,580 / 5,820 / 5,740, 128 x 512 x 1024 (5.1) 5,530 / 5,780 / 5,690, FP16 512^3
+  //   (5.1) 5,720 / 5,880 / 5,740; 320^3 FP32 (2.5, five 64s) 5,940 / 5,840, 640 x 512 x 512
+  //   FP16 (6.4, five 128s) 6,100 / 5,780.  Smaller: 256^3 FP32 (1.3) 5,780 / 5,770 / 5,570,
+  //   128x128x256 (0.3) 5,795 / 5,640 / 5,430.  FP64 gains and loses (384^3 5,380 / 5,490 /
+  //   5,500, 256 x 384 x 384 5,590 / 5,500 / 5,460).
+  const bool runs = sizeof(T) < 8 && (double)Q * (double)d.N * sizeof(T) > 2e9 && (gx < 5 || gx % 2 == 0);
+  const int run = gx > 1 && !lines ? 0 : (runs ? 128 : 1);
   const int tiles = gx * gy * d.nz;
-  const dim3 grid(chunk ? xcd_grid(tiles) : tiles);
+  const dim3 grid(run == 1 ? tiles : (run ? xcd_run_grid(tiles, run) : xcd_grid(tiles)));
   // Each value is read once, but a line that two waves share is read twice and
   // should still be cached then: plain loads (384^3 FP32 1.49 against 1.55 ms,
   // 320^3 826 against 933 us, 128x128x256 110 against 113 us).  At FP64 a wave
@@ -173,13 +197,13 @@ static void launch_sweep_t(const DevDomain& d, bool beside, hipStream_t s) {
   constexpr bool nt = sizeof(T) == 8;
   const unsigned lds = beside ? residency_lds(bx * by, sizeof(T) == 2 ? 24 : 20) : 0u;
   if (d.forced && lines)
-    hipLaunchKernelGGL((k_sweep<T, true, nt, true>), grid, block, lds, s, d, gx, gy, chunk);
+    hipLaunchKernelGGL((k_sweep<T, true, nt, true>), grid, block, lds, s, d, gx, gy, run);
   else if (d.forced)
-    hipLaunchKernelGGL((k_sweep<T, true, nt, false>), grid, block, lds, s, d, gx, gy, chunk);
+    hipLaunchKernelGGL((k_sweep<T, true, nt, false>), grid, block, lds, s, d, gx, gy, run);
   else if (lines)
-    hipLaunchKernelGGL((k_sweep<T, false, nt, true>), grid, block, lds, s, d, gx, gy, chunk);
+    hipLaunchKernelGGL((k_sweep<T, false, nt, true>), grid, block, lds, s, d, gx, gy, run);
   else
-    hipLaunchKernelGGL((k_sweep<T, false, nt, false>), grid, block, lds, s, d, gx, gy, chunk);
+    hipLaunchKernelGGL((k_sweep<T, false, nt, false>), grid, block, lds, s, d, gx, gy, run);
 }
 
 void launch_sweep(const DevDomain& d, bool beside, hipStream_t s) {
