@@ -130,8 +130,9 @@ typedef struct lbmdem_config {
                                run on a second, library-owned stream beside the
                                sweep (they need only the previous step's
                                forces); it waits on and rejoins the domain's
-                               stream within the step; lattices whose sweep is
-                               too short to hide them run them after it.  0:
+                               stream within the step; where that would not hide
+                               them (a short sweep; by direct launches, 33 to 64
+                               spheres) they run after the sweep.  0:
                                everything on the domain's stream.  Results are
                                identical.                                        */
   double body_force[3];     /* fluid body force a (force density, lattice units),

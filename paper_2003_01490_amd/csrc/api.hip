@@ -854,10 +854,19 @@ int32_t lbmdem_set_sphere_mode(lbmdem_domain* dom, int32_t id, int32_t mode, con
 // 65 / 48 us, 96x96x128 88 / 84, 96^3 FP64 with 156 spheres 300 / 283, 128^3
 // with 375 spheres 335 / 325, 128x128x256 144 / 163, 192^3 with 1,200 spheres
 // 484 / 512; graphs 32^3 49 / 49, 75x61x101 59 / 69, 96x96x128 76 / 89.  The
-// estimate is the sweep's bytes at 5.5 TB/s.
+// estimate is the sweep's bytes at 5.5 TB/s.  By direct launches the sweep's
+// blocks are there before the DEM has waited for the fork's event, and the
+// one-workgroup kernel of more than 32 spheres (512 threads, 30 to 58 KB of LDS)
+// finds no CU with room until the sweep ends: beside / after, 40 spheres 128x128x256
+// 188 / 178, 192^3 262 / 254, 256^3 522 / 511, 320^3 922 / 901 (32 spheres 156 / 181,
+// 226 / 257, 488 / 510, 878 / 909).  In a graph it starts first: 160 / 182, 234 / 260,
+// 504 / 518, 897 / 909.
 constexpr double OVERLAP_MIN_US = 80.0, OVERLAP_MIN_US_GRAPH = 10.0;
+constexpr int OVERLAP_MAX_LANES = 32;
 static bool overlap_step(const lbmdem_domain* dom, bool graph) {
   if (!dom->cfg.overlap || dom->d.P <= 0) return false;
+  if (!graph && dom->d.P > OVERLAP_MAX_LANES && dom->d.P <= DEM_LDS_MAX && !dem_many(dom->d, dom->cfg.dem_kernel))
+    return false;
   const double us = lbmdem_sweep_bytes(dom) / 5.5e6;
   return us >= (graph ? OVERLAP_MIN_US_GRAPH : OVERLAP_MIN_US);
 }
