@@ -280,7 +280,7 @@ const char* check_config(const lbmdem_config* c) {
   if (c->map_kernel == 3 && !fused_geom(*c).ok)
     return "map_kernel 3 needs a sphere radius of at least 1";
   if (c->map_kernel == 2 && !ball_possible(*c))
-    return "map_kernel 2 needs the staged cube (R_max + 4 cells each side) within 60000 bytes of LDS and "
+    return "map_kernel 2 needs the staged cube (R_max + 4 cells each side) within 60000 bytes of LDS (at 256 threads) and "
            "within every periodic extent";
   return nullptr;
 }

@@ -60,9 +60,9 @@ static __constant__ const double WQ[Q] = {1.0 / 3,  1.0 / 18, 1.0 / 18, 1.0 / 18
 
 // Step state of a domain, resident on the device so that a step needs no
 // per-step kernel arguments (graph replay, batched launches) and a domain can
-// stop on the device.  The DEM kernel (run every step, also without spheres)
-// advances it after the sweep: cur flips, stamp and steps increase, and the
-// stop rule is evaluated; a stop freezes the domain at the start of the next
+// stop on the device.  The step control at the end of a step (the last block of
+// the boundary pass, or a kernel of one thread) advances it: cur flips, stamp and
+// steps increase, and the stop rule is evaluated; a stop freezes the domain at the start of the next
 // step, before its mapping could change (that step's sweep output goes to the
 // spare buffer and is dropped).
 struct DevCtl {
@@ -189,9 +189,10 @@ __host__ __device__ inline long long cidx(const DevDomain& d, int i, int j, int 
 // i.e. the 19 x-rows of one (j, k) follow each other.  A sweep block then
 // streams through one contiguous run of 19 rows on the store side and nine
 // such runs on the load side, instead of 38 streams a whole plane of N cells
-// apart (sweep alone, 512^3: 3.50 against 3.66 ms FP32 and 1.78 against
-// 1.96 ms FP16; 384^3 FP32 1.43 against 1.54 ms; 128x128x256 106 against
-// 115 us FP32 and 214 against 227 us FP64).
+// apart (loads and stores of the sweep alone, without collision, in tiles of
+// 128 x 2: 512^3 3.50 against 3.66 ms FP32 and 1.78 against 1.96 ms FP16; 384^3 FP32
+// 1.43 against 1.54 ms; 128x128x256 106 against 115 us FP32 and 214 against 227 us
+// FP64; the sweep itself 3.52 against 3.80 ms at 512^3 FP32).
 __host__ __device__ inline size_t prow(const DevDomain& d, int j, int k) {
   return (size_t)Q * d.nx * ((size_t)j + (size_t)d.ny * (size_t)k);
 }

@@ -36,14 +36,14 @@ namespace lbmdem {
 // sweep_tiles), gx x gy tiles per z plane, x fastest, handed to the XCDs in
 // runs (see launch_sweep_t; 1: tile by tile, 0: one run each); the current
 // buffer is read from the domain's step state.  The 19 rows of a (y, z) lie next to each other, so a
-// block stores one contiguous run: 512^3 FP32 3.51-3.53 ms alone (5.8 TB/s)
+// block stores one contiguous run: 512^3 FP32 3.50-3.52 ms alone (5.85 TB/s)
 // against 3.80 with a plane of N cells per direction.
 constexpr int SWEEP_MAX_THREADS = 512;
 
 // Non-temporal stores where every row starts on a 64-byte piece.  Elsewhere the
 // line at the junction of two rows is written in two parts, which plain stores
 // let the L2 join: 75 x 61 x 101 FP32 22 -> 17 us, 429 x 151 x 100 277 -> 204,
-// 150 x 130 x 140 FP64 198 -> 190, the batch above 1.59 -> 1.33 ms (aligned
+// 150 x 130 x 140 FP64 198 -> 190, a batch of 16 requests 1.59 -> 1.35 ms (aligned
 // rows lose: 384^3 1.54 -> 1.64 ms, 128x128x256 FP64 220 -> 243 us, 200^3 FP64
 // 453 -> 482 us).  With a body force the same: aligned rows 128x128x256 FP64 246 ->
 // 220 us, 384^3 FP32 1.64 -> 1.50 ms with non-temporal stores.
@@ -152,7 +152,7 @@ void sweep_tiles(int nx, int ny, int storage, bool batch, int* bx, int* by, int*
 // LDS that a sweep block of so many threads asks for (and does not use) so that
 // at most `waves` wavefronts of the sweep are resident on a CU.  The sweep is
 // bound by bandwidth and needs no more; with eight of its waves on every SIMD
-// (60 VGPRs each at FP32) no registers are left for a DEM wave (130-240 VGPRs)
+// (60 VGPRs each at FP32) no registers are left for a DEM wave (163-250 VGPRs)
 // beside it, and the DEM chain waits for waves of the sweep to end together:
 // 24,000 spheres beside the 512^3 FP32 sweep, sub-cycle 213 -> 61 us, first
 // positions 1,000 -> 21 us, sweep 3.55 -> 3.52 ms; one sphere beside the
